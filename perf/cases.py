@@ -293,8 +293,8 @@ def work(case):
     V = dims[0] * dims[1] * dims[2] * dims[3]
     if kind == "apply":  # the fields in and out, the links
         return {"bytes": case["nrhs"] * 2 * V * 12 * 16 + 4 * V * 6 * BYTES[case["prec"]], "flops": case["nrhs"] * V * HOP_FLOPS}
-    if kind == "smear":  # every step reads and writes the fields; six colour products of four spins a site
-        return {"bytes": case["iters"] * (case["nrhs"] * 2 * V * 12 * 16 + 3 * V * 6 * 16),
+    if kind == "smear":  # the fields in and out and the spatial links; six colour products of four spins a site and step
+        return {"bytes": case["nrhs"] * 2 * V * 12 * 16 + 3 * V * 6 * 16,
                 "flops": case["iters"] * case["nrhs"] * V * (6 * 4 * 72 + 48)}
     if kind == "solve":
         b, f = _solve_work(V, case["nrhs"], case["tol"], case["prec"])
