@@ -225,9 +225,9 @@ typedef struct {
     double seconds;           /* this right-hand side's share of the wall time of its batch (the
                                  batch's time divided by its right-hand sides) */
     double bytes;             /* algorithmic bytes of its field operands: every operand of every kernel
-                                 its solve ran, moved once (per iteration 25 half fields for BiCGStab,
-                                 19 for CGNR, in the iteration precision; per reliable update 8 FP64
-                                 and 3 iteration-precision half fields; set-up and reconstruction); the
+                                 its solve ran, moved once (per iteration 23 half fields for BiCGStab,
+                                 16 for CGNR, in the iteration precision; per reliable update up to 9
+                                 FP64 and 7 iteration-precision half fields; set-up and reconstruction); the
                                  links, shared by the batch, are not counted */
 } dl_solve_stats;
 

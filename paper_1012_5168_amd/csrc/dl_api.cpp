@@ -813,7 +813,11 @@ struct SolveWork {
     int prec = P64;
     HalfField be, bo, bhat, x64, xo, r64, tmp64;     // FP64 (BiCGStab)
     HalfField r, rh, p, v, t, tmpo, xlo;             // iteration precision
-    DevBuf st, act, upd, restart, parts, parts2;
+    DevBuf st, flags, parts, parts2;
+    // per right-hand side flags, one array after the other: iterating, reliable update due, restart due
+    int *act() const { return flags.as<int>(); }
+    int *upd() const { return flags.as<int>() + n; }
+    int *restart() const { return flags.as<int>() + 2 * n; }
     int nblk_max = 0;
 
     void alloc_bicg(int prec_, int n_, int64_t Vh)
@@ -857,14 +861,12 @@ struct SolveWork {
     {
         nblk_max = (int)((Vh + 63) / 64);
         st.alloc(sizeof(KState) * n);
-        act.alloc(sizeof(int) * n);
-        upd.alloc(sizeof(int) * n);
-        restart.alloc(sizeof(int) * n);
-        // partial sums per (right-hand side, site block): up to five per block
+        flags.alloc(sizeof(int) * 3 * n);
+        // partial sums per (right-hand side, site block): up to seven per block
         // (the hop that makes t), and a second set that lives across a kernel
-        // in between ((rhat, s) of the s update, FP64 residual norms)
-        parts.alloc(sizeof(double) * 5 * (size_t)n * nblk_max);
-        parts2.alloc(sizeof(double) * 3 * (size_t)n * nblk_max);
+        // in between (FP64 residual norms)
+        parts.alloc(sizeof(double) * 7 * (size_t)n * nblk_max);
+        parts2.alloc(sizeof(double) * (size_t)n * nblk_max);
     }
     static size_t bytes_bicg(int prec, int64_t Vh)
     {
@@ -888,7 +890,7 @@ VSeg vs(std::initializer_list<Field> f, int64_t Vh, int n, const int *mask = nul
     VSeg a;
     int k = 0;
     for (const Field &x : f) a.f[k++] = x;
-    for (; k < 5; ++k) a.f[k] = NOF;
+    for (; k < 6; ++k) a.f[k] = NOF;
     a.st = st;
     a.mask = mask;
     a.Vh = Vh;
@@ -932,20 +934,18 @@ std::vector<DslashCall> DS(const std::vector<Prob> &P, F f)
     return v;
 }
 // scalar segments with the partials' block count per problem
-std::vector<SSeg> SS(const std::vector<Prob> &P, const std::vector<int> &nblk, bool second_parts, const int *(*mask)(
-                                                                                                       const Prob &))
+std::vector<SSeg> SS(const std::vector<Prob> &P, const std::vector<int> &nblk, const int *(*mask)(const Prob &) = nullptr)
 {
     std::vector<SSeg> v;
     for (size_t k = 0; k < P.size(); ++k) {
         SolveWork &w = *P[k].w;
         SSeg a;
         a.st = w.st.as<KState>();
-        a.act = w.act.as<int>();
-        a.upd = w.upd.as<int>();
-        a.restart = w.restart.as<int>();
+        a.act = w.act();
+        a.upd = w.upd();
+        a.restart = w.restart();
         a.mask = mask ? mask(P[k]) : nullptr;
         a.parts = w.parts.as<double>();
-        a.parts2 = second_parts ? w.parts2.as<double>() : nullptr;
         a.nblk = nblk[k];
         a.nrhs = w.n;
         v.push_back(a);
@@ -958,23 +958,23 @@ std::vector<int> blas_nb(const std::vector<Prob> &P)
     for (const Prob &p : P) v.push_back(p.nb());
     return v;
 }
-const int *mask_restart(const Prob &p) { return p.w->restart.as<int>(); }
+const int *mask_restart(const Prob &p) { return p.w->restart(); }
 
 // The launches of one BiCGStab iteration over all problems.  The search
 // direction p of this iteration is in place (from the previous iteration's
 // fused update, or p = r after a (re)start):
-//   v = Mhat p, alpha = rho / (rhat, v);  s = r - alpha v with (rhat, s);
+//   v = Mhat p, alpha = rho / (rhat, v);  s = r - alpha v;
 //   t = Mhat s, omega = (t, s) / |t|^2, rho' = (rhat, s) - omega (rhat, t),
 //   beta = (rho' / rho)(alpha / omega);
 //   x += alpha p + omega s, r = s - omega t, p = r + beta (p - omega v) in one
 //   pass with |r|^2; then the iteration count, convergence and reliable-update
 //   flags.  rho' follows from the linearity of (rhat, .) in r = s - omega t,
-//   which lets the p update join the x / r update (twelve field passes of
-//   vector kernels per iteration instead of fourteen, for one more read of
-//   rhat in the epilogue of the hop that makes t).
+//   which lets the p update join the x / r update; both of its dots are summed
+//   in the epilogue of the hop that makes t, which reads s anyway and rhat for
+//   them: eleven field passes of vector kernels per iteration.
 void bicg_iteration(const std::vector<Prob> &P, int prec, bool mixed, hipStream_t s)
 {
-    auto act = [](const Prob &p) { return p.w->act.as<int>(); };
+    auto act = [](const Prob &p) { return p.w->act(); };
     launch_dslash_batch(DS(P, [&](const Prob &p) {
                             return dcall(p.c, prec, 1, false, EPI_PLAIN, p.w->p.view(), p.w->tmpo.view(), NOF, NOF,
                                          1.0, p.w->n, nullptr, act(p));
@@ -987,10 +987,9 @@ void bicg_iteration(const std::vector<Prob> &P, int prec, bool mixed, hipStream_
                                                                 act(p));
                                                }),
                                                s);
-    scalar_launch(S_BICG_ALPHA, SS(P, nbd, false, nullptr), SParams{}, s);
+    scalar_launch(S_BICG_ALPHA, SS(P, nbd), SParams{}, s);
     vec_launch(V_BICG_S, prec, VS(P, [&](const Prob &p) {
-                   return vs({p.w->r.view(), p.w->v.view(), p.w->rh.view()}, p.Vh(), p.w->n, act(p),
-                             p.w->parts2.as<double>(), p.w->st.as<KState>());
+                   return vs({p.w->r.view(), p.w->v.view()}, p.Vh(), p.w->n, act(p), nullptr, p.w->st.as<KState>());
                }),
                s);
     launch_dslash_batch(DS(P, [&](const Prob &p) {
@@ -1004,9 +1003,7 @@ void bicg_iteration(const std::vector<Prob> &P, int prec, bool mixed, hipStream_
                                                p.w->parts.as<double>(), act(p));
                               }),
                               s);
-    std::vector<SSeg> om = SS(P, nbd, true, nullptr);
-    for (size_t k = 0; k < P.size(); ++k) om[k].nblk2 = P[k].nb();
-    scalar_launch(S_BICG_OMEGA, om, SParams{}, s);
+    scalar_launch(S_BICG_OMEGA, SS(P, nbd), SParams{}, s);
     vec_launch(V_BICG_XRP, prec, VS(P, [&](const Prob &p) {
                    Field xit = mixed ? p.w->xlo.view() : p.w->x64.view();
                    return vs({xit, p.w->r.view(), p.w->p.view(), p.w->t.view(), p.w->v.view()}, p.Vh(), p.w->n,
@@ -1015,24 +1012,28 @@ void bicg_iteration(const std::vector<Prob> &P, int prec, bool mixed, hipStream_
                s);
     SParams sp;
     sp.mixed = mixed ? 1 : 0;
-    scalar_launch(S_BICG_CHECK, SS(P, blas_nb(P), false, nullptr), sp, s);
+    scalar_launch(S_BICG_CHECK, SS(P, blas_nb(P)), sp, s);
 }
 
-int count_host(const DevBuf &flags, int n, hipStream_t s, std::vector<int> &h)
+// How many right-hand sides have each flag set: iterating, reliable update due, restart due.
+struct FlagCount {
+    int act = 0, upd = 0, restart = 0;
+};
+FlagCount count_flags(const std::vector<Prob> &P, hipStream_t s)
 {
-    h.resize(n);
-    DL_HIP(hipMemcpyAsync(h.data(), flags.p, sizeof(int) * n, hipMemcpyDeviceToHost, s));
+    FlagCount c;
+    std::vector<std::vector<int>> h(P.size());
+    for (size_t k = 0; k < P.size(); ++k) {
+        h[k].resize(3 * (size_t)P[k].w->n);
+        DL_HIP(hipMemcpyAsync(h[k].data(), P[k].w->flags.p, sizeof(int) * h[k].size(), hipMemcpyDeviceToHost, s));
+    }
     DL_HIP(hipStreamSynchronize(s));
-    int c = 0;
-    for (int v : h) c += v != 0;
-    return c;
-}
-
-int count_all(const std::vector<Prob> &P, bool upd, hipStream_t s)
-{
-    std::vector<int> h;
-    int c = 0;
-    for (const Prob &p : P) c += count_host(upd ? p.w->upd : p.w->act, p.w->n, s, h);
+    for (size_t k = 0; k < P.size(); ++k)
+        for (int i = 0, n = P[k].w->n; i < n; ++i) {
+            c.act += h[k][i] != 0;
+            c.upd += h[k][n + i] != 0;
+            c.restart += h[k][2 * n + i] != 0;
+        }
     return c;
 }
 
@@ -1136,41 +1137,30 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
     const int prec = P[0].w->prec;
     const bool mixed = prec != P64;
     const double delta = mixed ? (prm.delta > 0 ? prm.delta : 0.01) : 0.0;
-    auto upd = [](const Prob &p) { return (const int *)p.w->upd.as<int>(); };
+    auto upd = [](const Prob &p) { return (const int *)p.w->upd(); };
 
     // |b|^2 over both parities; bhat = b_e + kappa D_eo b_o
     vec_launch(V_NORM2, P64, VS(P, [&](const Prob &p) {
-                   return vs({p.w->be.view()}, p.Vh(), p.w->n, nullptr, p.w->parts.as<double>());
-               }),
-               s);
-    vec_launch(V_NORM2, P64, VS(P, [&](const Prob &p) {
-                   return vs({p.w->bo.view()}, p.Vh(), p.w->n, nullptr, p.w->parts2.as<double>());
+                   return vs({p.w->be.view(), p.w->bo.view()}, p.Vh(), p.w->n, nullptr, p.w->parts.as<double>());
                }),
                s);
     SParams sp;
     sp.tol2 = prm.tol * prm.tol;
     sp.delta2 = delta * delta;
     sp.maxiter = prm.maxiter;
-    scalar_launch(S_BICG_INIT, SS(P, blas_nb(P), true, nullptr), sp, s);
+    scalar_launch(S_BICG_INIT, SS(P, blas_nb(P)), sp, s);
     launch_dslash_batch(DS(P, [&](const Prob &p) {
                             return dcall(p.c, P64, 0, false, EPI_XPAY, p.w->bo.view(), p.w->bhat.view(),
                                          p.w->be.view(), NOF, p.kappa, p.w->n, nullptr, nullptr);
                         }),
                         s);
-    vec_launch(V_ZERO, P64, VS(P, [&](const Prob &p) { return vs({p.w->x64.view()}, p.Vh(), p.w->n); }), s);
-    if (mixed) vec_launch(V_ZERO, prec, VS(P, [&](const Prob &p) { return vs({p.w->xlo.view()}, p.Vh(), p.w->n); }), s);
-    copy_launch(prec, P64, VS(P, [&](const Prob &p) { return vs({p.w->r.view(), p.w->bhat.view()}, p.Vh(), p.w->n); }),
-                s);
-    copy_launch(prec, prec, VS(P, [&](const Prob &p) { return vs({p.w->rh.view(), p.w->r.view()}, p.Vh(), p.w->n); }),
-                s);
-    copy_launch(prec, prec, VS(P, [&](const Prob &p) { return vs({p.w->p.view(), p.w->r.view()}, p.Vh(), p.w->n); }),
-                s);
-    vec_launch(V_DOT, prec, VS(P, [&](const Prob &p) {
-                   return vs({p.w->rh.view(), p.w->r.view()}, p.Vh(), p.w->n, nullptr, p.w->parts.as<double>());
-               }),
-               s);
-    SParams sr;
-    scalar_launch(S_BICG_RHO, SS(P, blas_nb(P), false, nullptr), sr, s);
+    start_launch(prec, VS(P, [&](const Prob &p) {
+                     return vs({p.w->bhat.view(), p.w->r.view(), p.w->rh.view(), p.w->p.view(), p.w->x64.view(),
+                                mixed ? p.w->xlo.view() : NOF},
+                               p.Vh(), p.w->n, nullptr, p.w->parts.as<double>());
+                 }),
+                 s);
+    scalar_launch(S_BICG_RHO, SS(P, blas_nb(P)), SParams{}, s);
 
     const int poll = parse_poll(prm);
     int it = 0;
@@ -1198,7 +1188,8 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
         // into the FP64 x and the FP64 residual bhat - Mhat x recomputed; where
         // the true residual disagrees with a claimed convergence the recursion
         // restarts from it.
-        if (count_all(P, true, s) > 0) {
+        FlagCount fc = count_flags(P, s);
+        if (fc.upd > 0) {
             if (mixed)
                 fold_launch(prec, VS(P, [&](const Prob &p) {
                                 return vs({p.w->x64.view(), p.w->xlo.view()}, p.Vh(), p.w->n, upd(p));
@@ -1224,28 +1215,25 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
                                          p.w->n, upd(p), p.w->parts.as<double>());
                            }),
                            s);
-            scalar_launch(S_BICG_RESYNC, SS(P, blas_nb(P), false, upd), SParams{}, s);
-            // residual norms are in parts2 for this check
-            std::vector<SSeg> tr = SS(P, nb64, false, nullptr);
-            for (size_t k = 0; k < P.size(); ++k) tr[k].parts = P[k].w->parts2.as<double>();
-            scalar_launch(S_TRUE_RES, tr, SParams{}, s);
-            // restart from the true residual: rhat = r, p = r
-            copy_launch(prec, prec, VS(P, [&](const Prob &p) {
-                            return vs({p.w->rh.view(), p.w->r.view()}, p.Vh(), p.w->n, mask_restart(p));
-                        }),
-                        s);
-            copy_launch(prec, prec, VS(P, [&](const Prob &p) {
-                            return vs({p.w->p.view(), p.w->r.view()}, p.Vh(), p.w->n, mask_restart(p));
-                        }),
-                        s);
-            vec_launch(V_DOT, prec, VS(P, [&](const Prob &p) {
-                           return vs({p.w->rh.view(), p.w->r.view()}, p.Vh(), p.w->n, mask_restart(p),
-                                     p.w->parts.as<double>());
-                       }),
-                       s);
-            scalar_launch(S_BICG_RHO, SS(P, blas_nb(P), false, mask_restart), sr, s);
+            std::vector<SSeg> up = SS(P, blas_nb(P));
+            for (size_t k = 0; k < P.size(); ++k) {
+                up[k].parts2 = P[k].w->parts2.as<double>();
+                up[k].nblk2 = nb64[k];
+            }
+            scalar_launch(S_BICG_UPDATE, up, SParams{}, s);
+            fc = count_flags(P, s);
+            if (fc.restart > 0) {
+                // restart from the true residual: rhat = r, p = r
+                vec_launch(V_RESTART, prec, VS(P, [&](const Prob &p) {
+                               return vs({p.w->r.view(), p.w->rh.view(), p.w->p.view()}, p.Vh(), p.w->n,
+                                         mask_restart(p), p.w->parts.as<double>());
+                           }),
+                           s);
+                scalar_launch(S_BICG_RHO, SS(P, blas_nb(P), mask_restart), SParams{}, s);
+                fc = count_flags(P, s);
+            }
         }
-        if (count_all(P, false, s) == 0) break;
+        if (fc.act == 0) break;
     }
     // x_o = b_o + kappa D_oe x_e
     launch_dslash_batch(DS(P, [&](const Prob &p) {
@@ -1280,12 +1268,10 @@ void true_residual_full(const Ctx &c, double kappa, SolveWork &w, std::vector<do
     a.nblk = nbd;
     a.nrhs = n;
     a.out = sums.as<double>();
-    SParams sp;
-    sp.np = 1;
-    scalar_launch(S_SUM, {a}, sp, c.s);
+    scalar_launch(S_SUM, {a}, SParams{}, c.s);
     a.parts = parts2;
     a.out = sums.as<double>() + n;
-    scalar_launch(S_SUM, {a}, sp, c.s);
+    scalar_launch(S_SUM, {a}, SParams{}, c.s);
     std::vector<double> h(2 * n);
     DL_HIP(hipMemcpyAsync(h.data(), sums.p, sizeof(double) * 2 * n, hipMemcpyDeviceToHost, c.s));
     DL_HIP(hipStreamSynchronize(c.s));
@@ -1302,7 +1288,7 @@ void cgnr_batch(const Ctx &c, double kappa, int iters, SolveWork &w)
     const int64_t Vh = c.g.Vh;
     const int nb = blas_blocks(Vh);
     KState *st = w.st.as<KState>();
-    int *act = w.act.as<int>();
+    int *act = w.act();
     double *parts = w.parts.as<double>();
     const double k2 = kappa * kappa;
     auto sseg = [&](int nblk) {
@@ -1402,18 +1388,18 @@ struct Stopwatch {
 
 // Algorithmic bytes of one right-hand side's field operands in a solve: every
 // operand of every kernel the solve runs for it, moved once (the links, which
-// the whole batch shares, are not counted).  Per iteration: BiCGStab moves 24
+// the whole batch shares, are not counted).  Per iteration: BiCGStab moves 23
 // half fields in the iteration precision (the hops 2 + 4 + 2 + 4, the s
-// update 4, the fused x / r / p update 8); the truncated CGNR 16 (four hops
+// update 3, the fused x / r / p update 8); the truncated CGNR 16 (four hops
 // 2 + 3 + 2 + 4, the last of them forming q and updating r in its epilogue,
 // and the fused x and p update 5).  A reliable update moves 9 FP64 half
 // fields (2 for the fold, 2 + 4 for the FP64 residual hops, 1 for the
 // replacement of r) and 7 in the iteration precision (the fold 2, the
 // replacement of r and p with (rhat, r) 5); without iterations below FP64
 // there is no fold.  The set-up and the reconstruction of the odd sites move
-// 10 FP64 half fields (source norms 2, prepared source 3, zeroed x 1, the copy
-// into r 1, reconstruction 3) and 8 in the iteration precision (r, rhat = r,
-// p = r, the first dot, zeroed low-precision x).
+// 10 FP64 half fields (source norms 2, prepared source 3, the start 2: the
+// prepared source read and x cleared, reconstruction 3) and 4 in the iteration
+// precision (r, rhat, p and the low-precision x written by the start).
 double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
 {
     const double vh = (double)w.r.Vh;
@@ -1422,7 +1408,7 @@ double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
     const double f8 = vh * 12.0 * 16.0;
     const bool mixed = w.prec != P64;
     const double upd = mixed ? 9.0 * f8 + 7.0 * fb : 7.0 * f8 + 5.0 * fb;
-    return k.iters * 24.0 * fb + k.updates * upd + 10.0 * f8 + 8.0 * fb;
+    return k.iters * 23.0 * fb + k.updates * upd + 10.0 * f8 + 4.0 * fb;
 }
 
 // Per right-hand side statistics of the solve just finished; `seconds` is the

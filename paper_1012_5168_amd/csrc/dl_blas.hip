@@ -5,8 +5,8 @@
 // Every launch covers a batch of segments (one per lattice); a work item is
 // one (right-hand side, site block) of a segment, or one right-hand side for
 // the scalar kernels.  Reductions are deterministic: each site block writes
-// one partial per right-hand side, and a one-wave-per-right-hand-side kernel
-// sums the partials in a fixed order.  Items whose mask flag is clear return
+// one partial per right-hand side, and one workgroup per right-hand side sums
+// them in a fixed order.  Items whose mask flag is clear return
 // at once.
 #include <algorithm>
 
@@ -30,14 +30,53 @@ __device__ __forceinline__ void count_live(unsigned *live, int blk)
     if (live != nullptr && blk == 0 && threadIdx.x == 0) atomicAdd(live, 1u);
 }
 
-// ---------------------------------------------------------------- scalar kernels (one wave per rhs)
+// ---------------------------------------------------------------- scalar kernels (one workgroup per rhs)
 
-// sum of partials [rhs][nblk][np] component k, fixed order
-__device__ double sum_parts(const double *parts, int rhs, int nblk, int np, int k)
+constexpr int SCALAR_WAVES = 4;  // at most, per right-hand side
+
+// out[k] = sum over blocks of partials [rhs][nblk][NP] component k, in a fixed
+// order; valid in thread 0.  All components of a block's partial are read
+// together (they are neighbours in memory) and four blocks are in flight per
+// lane, so the sum costs a few memory latencies instead of one per component
+// and 64 blocks: with one wavefront per right-hand side and a component at a
+// time the omega step of 24 right-hand sides at 24^3 x 48 (5184 blocks, seven
+// sums) took 81 us, see scalar_threads for the wavefronts.
+template <int NP>
+__device__ void sum_parts(const double *parts, int rhs, int nblk, double out[NP])
 {
-    double s = 0;
-    for (int b = threadIdx.x; b < nblk; b += 64) s += parts[((int64_t)rhs * nblk + b) * np + k];
-    return wave_sum(s);
+    __shared__ double red[SCALAR_WAVES * NP];
+    const double *q = parts + (int64_t)rhs * nblk * NP;
+    const int bd = blockDim.x;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) out[k] = 0;
+    int b = threadIdx.x;
+    for (; b + 3 * bd < nblk; b += 4 * bd) {
+        double v[4][NP];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < NP; ++k) v[u][k] = q[(int64_t)(b + u * bd) * NP + k];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < NP; ++k) out[k] += v[u][k];
+    }
+    for (; b < nblk; b += bd)
+#pragma unroll
+        for (int k = 0; k < NP; ++k) out[k] += q[(int64_t)b * NP + k];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) out[k] = wave_sum(out[k]);
+    if (bd == 64) return;
+    const int wid = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < NP; ++k) red[wid * NP + k] = out[k];
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            for (int w = 1; w < (bd >> 6); ++w) out[k] += red[w * NP + k];
+    __syncthreads();  // the next sum may overwrite red
 }
 
 __device__ __forceinline__ void cdiv(const double a[2], const double b[2], double out[2])
@@ -56,8 +95,8 @@ __device__ __forceinline__ void cmul(const double a[2], const double b[2], doubl
 
 __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
 {
-    double b2 = sum_parts(a.parts, rhs, a.nblk, 1, 0);
-    if (a.parts2) b2 += sum_parts(a.parts2, rhs, a.nblk, 1, 0);
+    double b2;
+    sum_parts<1>(a.parts, rhs, a.nblk, &b2);
     if (threadIdx.x != 0) return;
     KState s = {};
     s.rho[0] = s.alpha[0] = s.omega[0] = 1.0;
@@ -69,14 +108,16 @@ __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
     a.st[rhs] = s;
     a.act[rhs] = b2 > 0 ? 1 : 0;
     a.upd[rhs] = 0;
+    a.restart[rhs] = 0;
 }
 
 // (Re)start of the recursion: rho = (rhat, r) from partials [.., 2] (with
 // rhat = r, so |r|^2 is its real part), alpha = omega = 1.
-__device__ void bicg_rho(const SSeg &a, const SParams &p, int rhs)
+__device__ void bicg_rho(const SSeg &a, int rhs)
 {
     if (masked_off(a.mask, rhs)) return;
-    double rn[2] = {sum_parts(a.parts, rhs, a.nblk, 2, 0), sum_parts(a.parts, rhs, a.nblk, 2, 1)};
+    double rn[2];
+    sum_parts<2>(a.parts, rhs, a.nblk, rn);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     s.rho[0] = rn[0];
@@ -101,7 +142,8 @@ __device__ void bicg_rho(const SSeg &a, const SParams &p, int rhs)
 __device__ void bicg_check(const SSeg &a, const SParams &p, int rhs)
 {
     if (!a.act[rhs]) return;
-    const double rr = sum_parts(a.parts, rhs, a.nblk, 1, 0);
+    double rr;
+    sum_parts<1>(a.parts, rhs, a.nblk, &rr);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     s.iters += 1;
@@ -127,7 +169,8 @@ __device__ void bicg_check(const SSeg &a, const SParams &p, int rhs)
 __device__ void bicg_alpha(const SSeg &a, int rhs)
 {
     if (!a.act[rhs]) return;
-    double rv[2] = {sum_parts(a.parts, rhs, a.nblk, 2, 0), sum_parts(a.parts, rhs, a.nblk, 2, 1)};
+    double rv[2];
+    sum_parts<2>(a.parts, rhs, a.nblk, rv);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     cdiv(s.rho, rv, s.alpha);
@@ -135,22 +178,24 @@ __device__ void bicg_alpha(const SSeg &a, int rhs)
     a.st[rhs] = s;
 }
 
-// omega = (t, s) / |t|^2 from the partials of the hop that made t ([.., 5]:
-// (t, s), |t|^2, (rhat, t)); the next rho by linearity of r = s - omega t,
-// rho' = (rhat, s) - omega (rhat, t), with (rhat, s) from parts2 [.., 2] (the
-// s update); beta = (rho' / rho) (alpha / omega).  Each dot is taken directly
-// from the vectors of this iteration: nothing accumulates across iterations.
+// omega = (t, s) / |t|^2 from the partials of the hop that made t ([.., 7]:
+// (t, s), |t|^2, (rhat, t), (rhat, s)); the next rho by linearity of
+// r = s - omega t, rho' = (rhat, s) - omega (rhat, t); beta = (rho' / rho)
+// (alpha / omega).  Each dot is taken directly from the vectors of this
+// iteration: nothing accumulates across iterations.  (rhat, s) is zero but for
+// rounding, and it is kept: without it a right-hand side near breakdown lost
+// its way (7.9e-9 after 2000 iterations at a tolerance of 1e-12).  The hop's
+// epilogue reads both of its vectors anyway, so the s update, which summed it
+// before, moves three half fields instead of four.
 // omega = 0 (t = 0, e.g. s = 0 after an exact half step) ends the recursion:
 // beta is set to 0, and the check sends the right-hand side to the FP64 true
 // residual, which either confirms convergence or restarts from it.
 __device__ void bicg_omega(const SSeg &a, int rhs)
 {
     if (!a.act[rhs]) return;
-    const int nb2 = a.nblk2 > 0 ? a.nblk2 : a.nblk;
-    double ts[2] = {sum_parts(a.parts, rhs, a.nblk, 5, 0), sum_parts(a.parts, rhs, a.nblk, 5, 1)};
-    double tt = sum_parts(a.parts, rhs, a.nblk, 5, 2);
-    double rt[2] = {sum_parts(a.parts, rhs, a.nblk, 5, 3), sum_parts(a.parts, rhs, a.nblk, 5, 4)};
-    double rs[2] = {sum_parts(a.parts2, rhs, nb2, 2, 0), sum_parts(a.parts2, rhs, nb2, 2, 1)};
+    double d[7];
+    sum_parts<7>(a.parts, rhs, a.nblk, d);
+    const double ts[2] = {d[0], d[1]}, tt = d[2], rt[2] = {d[3], d[4]}, rs[2] = {d[5], d[6]};
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     if (tt > 0) {
@@ -175,29 +220,23 @@ __device__ void bicg_omega(const SSeg &a, int rhs)
     a.st[rhs] = s;
 }
 
-// After a reliable update replaced r by the FP64 residual (partials [.., 2]:
-// (rhat, r) of the replaced r): rho takes that value, so that the next alpha
-// matches the r it multiplies; alpha, omega and beta stay.
-__device__ void bicg_resync(const SSeg &a, int rhs)
-{
-    if (masked_off(a.mask, rhs)) return;
-    double rn[2] = {sum_parts(a.parts, rhs, a.nblk, 2, 0), sum_parts(a.parts, rhs, a.nblk, 2, 1)};
-    if (threadIdx.x != 0) return;
-    a.st[rhs].rho[0] = rn[0];
-    a.st[rhs].rho[1] = rn[1];
-}
-
-// after an FP64 residual recomputation (parts: |r_e|^2 [, parts2: |r_o|^2])
-__device__ void true_residual(const SSeg &a, const SParams &p, int rhs)
+// After a reliable update replaced r by the FP64 residual: partials [.., 2]
+// (rhat, r) of the replaced r, which rho takes, so that the next alpha matches
+// the r it multiplies (alpha, omega and beta stay); partials2 [.., 1] |r|^2 of
+// the FP64 residual, the true residual of the Schur system.
+__device__ void bicg_update(const SSeg &a, int rhs)
 {
     if (!a.upd[rhs]) {
         if (threadIdx.x == 0) a.restart[rhs] = 0;
         return;
     }
-    double r2 = sum_parts(a.parts, rhs, a.nblk, 1, 0);
-    if (a.parts2) r2 += sum_parts(a.parts2, rhs, a.nblk, 1, 0);
+    double rn[2], r2;
+    sum_parts<2>(a.parts, rhs, a.nblk, rn);
+    sum_parts<1>(a.parts2, rhs, a.nblk2, &r2);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
+    s.rho[0] = rn[0];
+    s.rho[1] = rn[1];
     s.true2 = r2;
     s.updates += 1;
     a.restart[rhs] = 0;
@@ -207,7 +246,7 @@ __device__ void true_residual(const SSeg &a, const SParams &p, int rhs)
     } else if (r2 <= s.stop2) {
         s.done = 1;
         a.act[rhs] = 0;
-    } else if (!a.act[rhs] && !p.final_check && s.iters < s.maxiter) {
+    } else if (!a.act[rhs] && s.iters < s.maxiter) {
         // the iterated residual claimed convergence but the true one disagrees:
         // restart the recursion from the true residual
         a.act[rhs] = 1;
@@ -221,7 +260,8 @@ __device__ void true_residual(const SSeg &a, const SParams &p, int rhs)
 
 __device__ void cg_init(const SSeg &a, const SParams &p, int rhs)
 {
-    double rr = sum_parts(a.parts, rhs, a.nblk, 1, 0);
+    double rr;
+    sum_parts<1>(a.parts, rhs, a.nblk, &rr);
     if (threadIdx.x != 0) return;
     KState s = {};
     s.rr = rr;
@@ -238,7 +278,8 @@ __device__ void cg_alpha(const SSeg &a, int rhs)
         if (threadIdx.x == 0) a.act[rhs] = 0;
         return;
     }
-    double pq = sum_parts(a.parts, rhs, a.nblk, 1, 0);
+    double pq;
+    sum_parts<1>(a.parts, rhs, a.nblk, &pq);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     if (pq > 0) {
@@ -254,7 +295,8 @@ __device__ void cg_alpha(const SSeg &a, int rhs)
 __device__ void cg_beta(const SSeg &a, int rhs)
 {
     if (!a.act[rhs]) return;
-    double rr = sum_parts(a.parts, rhs, a.nblk, 1, 0);
+    double rr;
+    sum_parts<1>(a.parts, rhs, a.nblk, &rr);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     s.beta[0] = s.rr > 0 ? rr / s.rr : 0;
@@ -266,29 +308,27 @@ __device__ void cg_beta(const SSeg &a, int rhs)
     a.st[rhs] = s;
 }
 
-__device__ void sum_out(const SSeg &a, const SParams &p, int rhs)
+__device__ void sum_out(const SSeg &a, int rhs)
 {
-    for (int k = 0; k < p.np; ++k) {
-        double v = sum_parts(a.parts, rhs, a.nblk, p.np, k);
-        if (threadIdx.x == 0) a.out[rhs * p.np + k] = v;
-    }
+    double v;
+    sum_parts<1>(a.parts, rhs, a.nblk, &v);
+    if (threadIdx.x == 0) a.out[rhs] = v;
 }
 
 template <int OP>
-__global__ __launch_bounds__(64) void scalar_kernel(Segs<SSeg> B, SParams p)
+__global__ __launch_bounds__(64 * SCALAR_WAVES) void scalar_kernel(Segs<SSeg> B, SParams p)
 {
     for_each_item(B, [&](const SSeg &a, int rhs) {
         if constexpr (OP == S_BICG_INIT) bicg_init(a, p, rhs);
-        else if constexpr (OP == S_BICG_RHO) bicg_rho(a, p, rhs);
+        else if constexpr (OP == S_BICG_RHO) bicg_rho(a, rhs);
         else if constexpr (OP == S_BICG_ALPHA) bicg_alpha(a, rhs);
         else if constexpr (OP == S_BICG_OMEGA) bicg_omega(a, rhs);
         else if constexpr (OP == S_BICG_CHECK) bicg_check(a, p, rhs);
-        else if constexpr (OP == S_BICG_RESYNC) bicg_resync(a, rhs);
-        else if constexpr (OP == S_TRUE_RES) true_residual(a, p, rhs);
+        else if constexpr (OP == S_BICG_UPDATE) bicg_update(a, rhs);
         else if constexpr (OP == S_CG_INIT) cg_init(a, p, rhs);
         else if constexpr (OP == S_CG_ALPHA) cg_alpha(a, rhs);
         else if constexpr (OP == S_CG_BETA) cg_beta(a, rhs);
-        else sum_out(a, p, rhs);
+        else sum_out(a, rhs);
     });
 }
 
@@ -305,14 +345,13 @@ __device__ __forceinline__ void write_parts(double v[NP], double *red, double *p
 }
 
 // f[0..4] by operation:
-//   V_BICG_S   s = r - alpha v (in r's storage); parts (rhat, s)                   f: r, v, rhat
+//   V_BICG_S   s = r - alpha v (in r's storage)                                     f: r, v
 //   V_BICG_XRP x += alpha p + omega s; r = s - omega t; p = r + beta (p - omega v);
 //              parts |r|^2                                                          f: x, r(s), p, t, v
-//   V_CG_XR    r -= alpha q; parts |r|^2                                            f: r, q
 //   V_CG_P     x += alpha p; p = r + beta p                                         f: p, r, x
 //   V_ZERO     f0 = 0
-//   V_NORM2    parts |f0|^2
-//   V_DOT      parts (f0, f1)
+//   V_NORM2    parts |f0|^2 + |f1|^2
+//   V_RESTART  rhat = p = r; parts (rhat, r)                                        f: r, rhat, p
 template <typename S, int OP>
 __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
 {
@@ -325,22 +364,14 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
     const int64_t cb = (int64_t)blk * BS + threadIdx.x;
     const bool valid = cb < Vh;
     if constexpr (OP == V_BICG_S) {
-        double part[2] = {0, 0};
-        if (valid) {
-            const cx<R> alpha = ld_c<R>(a.st[rhs].alpha);
-            cx<R> rv[12], vv[12], hv[12];
-            load_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
-            load_spinor<S, true>(a.f[1], Vh, rhs, cb, vv);
-            load_spinor<S, true>(a.f[2], Vh, rhs, cb, hv);
+        if (!valid) return;
+        const cx<R> alpha = ld_c<R>(a.st[rhs].alpha);
+        cx<R> rv[12], vv[12];
+        load_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
+        load_spinor<S, true>(a.f[1], Vh, rhs, cb, vv);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) {
-                rv[e] = rv[e] - alpha * vv[e];
-                part[0] += (double)hv[e].re * rv[e].re + (double)hv[e].im * rv[e].im;
-                part[1] += (double)hv[e].re * rv[e].im - (double)hv[e].im * rv[e].re;
-            }
-            store_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
-        }
-        write_parts<2>(part, red, a.parts, rhs, nb, blk);
+        for (int e = 0; e < 12; ++e) rv[e] = rv[e] - alpha * vv[e];
+        store_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
     } else if constexpr (OP == V_BICG_XRP) {
         double part[1] = {0};
         if (valid) {
@@ -362,21 +393,6 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
             store_spinor<S, true>(a.f[0], Vh, rhs, cb, xv);
             store_spinor<S, true>(a.f[1], Vh, rhs, cb, sv);
             store_spinor<S, true>(a.f[2], Vh, rhs, cb, pv);
-        }
-        write_parts<1>(part, red, a.parts, rhs, nb, blk);
-    } else if constexpr (OP == V_CG_XR) {
-        double part[1] = {0};
-        if (valid) {
-            const R alpha = R(a.st[rhs].alpha[0]);
-            cx<R> rv[12], qv[12];
-            load_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
-            load_spinor<S, true>(a.f[1], Vh, rhs, cb, qv);
-#pragma unroll
-            for (int e = 0; e < 12; ++e) {
-                rv[e] = rv[e] - alpha * qv[e];
-                part[0] += (double)rv[e].re * rv[e].re + (double)rv[e].im * rv[e].im;
-            }
-            store_spinor<S, true>(a.f[0], Vh, rhs, cb, rv);
         }
         write_parts<1>(part, red, a.parts, rhs, nb, blk);
     } else if constexpr (OP == V_CG_P) {
@@ -402,23 +418,24 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
     } else if constexpr (OP == V_NORM2) {
         double part[1] = {0};
         if (valid) {
-            cx<R> v[12];
+            cx<R> v[12], w[12];
             load_spinor<S, true>(a.f[0], Vh, rhs, cb, v);
+            load_spinor<S, true>(a.f[1], Vh, rhs, cb, w);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) part[0] += (double)v[e].re * v[e].re + (double)v[e].im * v[e].im;
+            for (int e = 0; e < 12; ++e)
+                part[0] += ((double)v[e].re * v[e].re + (double)v[e].im * v[e].im) +
+                           ((double)w[e].re * w[e].re + (double)w[e].im * w[e].im);
         }
         write_parts<1>(part, red, a.parts, rhs, nb, blk);
-    } else if constexpr (OP == V_DOT) {
+    } else if constexpr (OP == V_RESTART) {
         double part[2] = {0, 0};
         if (valid) {
-            cx<R> av[12], bv[12];
-            load_spinor<S, true>(a.f[0], Vh, rhs, cb, av);
-            load_spinor<S, true>(a.f[1], Vh, rhs, cb, bv);
+            cx<R> v[12];
+            load_spinor<S, true>(a.f[0], Vh, rhs, cb, v);
+            store_spinor<S, true>(a.f[1], Vh, rhs, cb, v);
+            store_spinor<S, true>(a.f[2], Vh, rhs, cb, v);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) {
-                part[0] += (double)av[e].re * bv[e].re + (double)av[e].im * bv[e].im;
-                part[1] += (double)av[e].re * bv[e].im - (double)av[e].im * bv[e].re;
-            }
+            for (int e = 0; e < 12; ++e) part[0] += (double)v[e].re * v[e].re + (double)v[e].im * v[e].im;
         }
         write_parts<2>(part, red, a.parts, rhs, nb, blk);
     }
@@ -515,22 +532,44 @@ __global__ __launch_bounds__(BS) void replace_kernel(Segs<VSeg> B)
     });
 }
 
-// f0 = f1 - f2 (FP64)
-__global__ __launch_bounds__(BS) void sub_kernel(Segs<VSeg> B)
+// The start of BiCGStab from the FP64 prepared source f0: r (f1) = rhat (f2) =
+// p (f3) = f0 in the iteration precision, the FP64 solution f4 = 0 and below
+// FP64 the low-precision iterate f5 = 0; parts (rhat, r).  One pass instead of
+// two copies of r, a conversion, two clears and a dot product.
+template <typename S>
+__global__ __launch_bounds__(BS) void start_kernel(Segs<VSeg> B)
 {
+    using R = typename Fmt<S>::R;
+    __shared__ double red[2 * (BS / 64)];
     for_each_item(B, [&](const VSeg &a, int item) {
         const int nb = (int)((a.Vh + BS - 1) / BS);
         const int rhs = item / nb, blk = item - rhs * nb;
-        if (masked_off(a.mask, rhs)) return;
         count_live(a.live, blk);
         const int64_t cb = (int64_t)blk * BS + threadIdx.x;
-        if (cb >= a.Vh) return;
-        cx<double> av[12], bv[12];
-        load_spinor<double>(a.f[1], a.Vh, rhs, cb, av);
-        load_spinor<double>(a.f[2], a.Vh, rhs, cb, bv);
+        double part[2] = {0, 0};
+        if (cb < a.Vh) {
+            cx<double> bv[12];
+            cx<R> v[12];
+            load_spinor<double, true>(a.f[0], a.Vh, rhs, cb, bv);
 #pragma unroll
-        for (int e = 0; e < 12; ++e) av[e] = av[e] - bv[e];
-        store_spinor<double, true>(a.f[0], a.Vh, rhs, cb, av);
+            for (int e = 0; e < 12; ++e) v[e] = {R(bv[e].re), R(bv[e].im)};
+            store_spinor<S>(a.f[1], a.Vh, rhs, cb, v);
+            // the 16-bit formats round in the store: rhat, p and the norm are of the stored r
+            if constexpr (Fmt<S>::VEC == 4) load_spinor<S>(a.f[1], a.Vh, rhs, cb, v);
+            store_spinor<S, true>(a.f[2], a.Vh, rhs, cb, v);
+            store_spinor<S, true>(a.f[3], a.Vh, rhs, cb, v);
+#pragma unroll
+            for (int e = 0; e < 12; ++e) part[0] += (double)v[e].re * v[e].re + (double)v[e].im * v[e].im;
+#pragma unroll
+            for (int e = 0; e < 12; ++e) bv[e] = {0.0, 0.0};
+            store_spinor<double, true>(a.f[4], a.Vh, rhs, cb, bv);
+            if (a.f[5].d != nullptr) {
+#pragma unroll
+                for (int e = 0; e < 12; ++e) v[e] = {R(0), R(0)};
+                store_spinor<S, true>(a.f[5], a.Vh, rhs, cb, v);
+            }
+        }
+        write_parts<2>(part, red, a.parts, rhs, nb, blk);
     });
 }
 
@@ -602,28 +641,39 @@ void copy_from(int prec_src, const Segs<VSeg> &B, int grid, hipStream_t s)
 
 int blas_blocks(int64_t Vh) { return (int)((Vh + BS - 1) / BS); }
 
+// Wavefronts that sum a right-hand side's partials: one up to 512 blocks (eight
+// partials a lane), four above, where the sums of one wavefront are a chain of
+// memory latencies.  The truncated CGNR's two sums keep one at every size: the
+// order of a sum then stays what its stored reference loops were made with.
+static int scalar_threads(int op, const std::vector<SSeg> &segs)
+{
+    if (op == S_CG_INIT || op == S_CG_ALPHA || op == S_CG_BETA) return 64;
+    int nblk = 0;
+    for (const SSeg &a : segs) nblk = std::max(nblk, std::max(a.nblk, a.nblk2));
+    return nblk > 512 ? 64 * SCALAR_WAVES : 64;
+}
+
 void scalar_launch(int op, const std::vector<SSeg> &segs, const SParams &p, hipStream_t s)
 {
     Segs<SSeg> B = make_segs(segs, scalar_items);
-    const int grid = grid_for(B.prefix[B.n], PERSIST);
+    const dim3 grid(grid_for(B.prefix[B.n], PERSIST)), bd(scalar_threads(op, segs));
     switch (op) {
-    case S_BICG_INIT: hipLaunchKernelGGL(scalar_kernel<S_BICG_INIT>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_BICG_RHO: hipLaunchKernelGGL(scalar_kernel<S_BICG_RHO>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_BICG_ALPHA: hipLaunchKernelGGL(scalar_kernel<S_BICG_ALPHA>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_BICG_OMEGA: hipLaunchKernelGGL(scalar_kernel<S_BICG_OMEGA>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_BICG_CHECK: hipLaunchKernelGGL(scalar_kernel<S_BICG_CHECK>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_BICG_RESYNC: hipLaunchKernelGGL(scalar_kernel<S_BICG_RESYNC>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_TRUE_RES: hipLaunchKernelGGL(scalar_kernel<S_TRUE_RES>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_CG_INIT: hipLaunchKernelGGL(scalar_kernel<S_CG_INIT>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_CG_ALPHA: hipLaunchKernelGGL(scalar_kernel<S_CG_ALPHA>, dim3(grid), dim3(64), 0, s, B, p); break;
-    case S_CG_BETA: hipLaunchKernelGGL(scalar_kernel<S_CG_BETA>, dim3(grid), dim3(64), 0, s, B, p); break;
-    default: hipLaunchKernelGGL(scalar_kernel<S_SUM>, dim3(grid), dim3(64), 0, s, B, p); break;
+    case S_BICG_INIT: hipLaunchKernelGGL(scalar_kernel<S_BICG_INIT>, grid, bd, 0, s, B, p); break;
+    case S_BICG_RHO: hipLaunchKernelGGL(scalar_kernel<S_BICG_RHO>, grid, bd, 0, s, B, p); break;
+    case S_BICG_ALPHA: hipLaunchKernelGGL(scalar_kernel<S_BICG_ALPHA>, grid, bd, 0, s, B, p); break;
+    case S_BICG_OMEGA: hipLaunchKernelGGL(scalar_kernel<S_BICG_OMEGA>, grid, bd, 0, s, B, p); break;
+    case S_BICG_CHECK: hipLaunchKernelGGL(scalar_kernel<S_BICG_CHECK>, grid, bd, 0, s, B, p); break;
+    case S_BICG_UPDATE: hipLaunchKernelGGL(scalar_kernel<S_BICG_UPDATE>, grid, bd, 0, s, B, p); break;
+    case S_CG_INIT: hipLaunchKernelGGL(scalar_kernel<S_CG_INIT>, grid, bd, 0, s, B, p); break;
+    case S_CG_ALPHA: hipLaunchKernelGGL(scalar_kernel<S_CG_ALPHA>, grid, bd, 0, s, B, p); break;
+    case S_CG_BETA: hipLaunchKernelGGL(scalar_kernel<S_CG_BETA>, grid, bd, 0, s, B, p); break;
+    default: hipLaunchKernelGGL(scalar_kernel<S_SUM>, grid, bd, 0, s, B, p); break;
     }
 }
 
 void vec_launch(int op, int prec, const std::vector<VSeg> &segs, hipStream_t s)
 {
-    static const int nvec[] = {4, 8, 3, 5, 1, 1, 2};
+    static const int nvec[] = {3, 8, 5, 1, 2, 3};
     ProfScope ps(PROF_BLAS, vec_bytes(prec, segs, nvec[op]), s);
     const std::vector<VSeg> sg =
         counted_segs(segs, ps, s, [&](int64_t Vh) { return nvec[op] * field_rhs_bytes(prec, Vh); });
@@ -632,11 +682,26 @@ void vec_launch(int op, int prec, const std::vector<VSeg> &segs, hipStream_t s)
     switch (op) {
     case V_BICG_S: vec_dispatch<V_BICG_S>(prec, B, grid, s); break;
     case V_BICG_XRP: vec_dispatch<V_BICG_XRP>(prec, B, grid, s); break;
-    case V_CG_XR: vec_dispatch<V_CG_XR>(prec, B, grid, s); break;
     case V_CG_P: vec_dispatch<V_CG_P>(prec, B, grid, s); break;
     case V_ZERO: vec_dispatch<V_ZERO>(prec, B, grid, s); break;
     case V_NORM2: vec_dispatch<V_NORM2>(prec, B, grid, s); break;
-    default: vec_dispatch<V_DOT>(prec, B, grid, s); break;
+    default: vec_dispatch<V_RESTART>(prec, B, grid, s); break;
+    }
+}
+
+void start_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s)
+{
+    const int n64 = 2, nlo = prec == P64 ? 3 : 4;
+    ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, n64) + vec_bytes(prec, segs, nlo), s);
+    const std::vector<VSeg> sg = counted_segs(
+        segs, ps, s, [&](int64_t Vh) { return n64 * field_rhs_bytes(P64, Vh) + nlo * field_rhs_bytes(prec, Vh); });
+    Segs<VSeg> B = make_segs(sg, vec_items);
+    const dim3 grid(grid_for(B.prefix[B.n], PERSIST));
+    switch (prec) {
+    case P64: hipLaunchKernelGGL(start_kernel<double>, grid, dim3(BS), 0, s, B); break;
+    case P32: hipLaunchKernelGGL(start_kernel<float>, grid, dim3(BS), 0, s, B); break;
+    case P16: hipLaunchKernelGGL(start_kernel<__half>, grid, dim3(BS), 0, s, B); break;
+    default: hipLaunchKernelGGL(start_kernel<__hip_bfloat16>, grid, dim3(BS), 0, s, B); break;
     }
 }
 
@@ -758,14 +823,6 @@ void stream_launch(int mode, const void *src, void *dst, int64_t nwords, hipStre
         hipLaunchKernelGGL(stream_kernel<0>, dim3(grid), dim3(256), 0, s, a, b, nwords);
     else
         hipLaunchKernelGGL(stream_kernel<1>, dim3(grid), dim3(256), 0, s, a, b, nwords);
-}
-
-void sub_launch(const std::vector<VSeg> &segs, hipStream_t s)
-{
-    ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, 3), s);
-    const std::vector<VSeg> sg = counted_segs(segs, ps, s, [&](int64_t Vh) { return 3 * field_rhs_bytes(P64, Vh); });
-    Segs<VSeg> B = make_segs(sg, vec_items);
-    hipLaunchKernelGGL(sub_kernel, dim3(grid_for(B.prefix[B.n], PERSIST)), dim3(BS), 0, s, B);
 }
 
 }  // namespace dl

@@ -176,7 +176,7 @@ template <int EPI>
 constexpr int nparts_c()
 {
     return EPI == EPI_XPAY_DOT ? 2
-           : EPI == EPI_XPAY_TS ? 5
+           : EPI == EPI_XPAY_TS ? 7
            : (EPI == EPI_XPAY_NRM || EPI == EPI_XMY_NRM || EPI == EPI_CG_R) ? 1
                                                                            : 0;
 }
@@ -247,7 +247,7 @@ __device__ __forceinline__ void epilogue_apply(const DKArgs &a, int rhs, int64_t
             o[e].re = fma(coef, acc[e].re, xv[e].re);
             o[e].im = fma(coef, acc[e].im, xv[e].im);
         }
-        double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0, p4 = 0.0;
+        double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0, p4 = 0.0, p5 = 0.0, p6 = 0.0;
         if constexpr (EPI == EPI_XPAY_DOT) {
 #pragma unroll
             for (int e = 0; e < 12; ++e) {
@@ -262,6 +262,8 @@ __device__ __forceinline__ void epilogue_apply(const DKArgs &a, int rhs, int64_t
                 p2 += (double)o[e].re * o[e].re + (double)o[e].im * o[e].im;
                 p3 += (double)ops.y[e].re * o[e].re + (double)ops.y[e].im * o[e].im;
                 p4 += (double)ops.y[e].re * o[e].im - (double)ops.y[e].im * o[e].re;
+                p5 += (double)ops.y[e].re * xv[e].re + (double)ops.y[e].im * xv[e].im;
+                p6 += (double)ops.y[e].re * xv[e].im - (double)ops.y[e].im * xv[e].re;
             }
         }
         if constexpr (EPI == EPI_CG_R) {
@@ -283,6 +285,8 @@ __device__ __forceinline__ void epilogue_apply(const DKArgs &a, int rhs, int64_t
                 part[2] += p2;
                 part[3] += p3;
                 part[4] += p4;
+                part[5] += p5;
+                part[6] += p6;
             }
         }
     }
