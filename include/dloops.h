@@ -480,8 +480,9 @@ int64_t dl_profile_read(int32_t kind, double *ms, double *bytes);
  * LDS and cfg[1] wavefronts walking the right-hand sides), cfg[2] = sites per
  * workgroup (item kernel) or the wavefronts per SIMD the LDS-link kernel
  * allows (0 = as compiled), cfg[3] = persistent grid cap (item kernel, 0 =
- * none) or region size in site blocks (LDS-link kernel).  cfg (host, 4
- * int32) is all -1 when no such launch was profiled since
+ * none) or region size in site blocks (LDS-link kernel); kernel 2 = FP64
+ * operators on canonical fields (dl_apply), cfg[1] wavefronts sharing a site
+ * block's right-hand sides, cfg[2] = sites per workgroup.  cfg (host, 4 int32) is all -1 when no such launch was profiled since
  * dl_profile_enable(1).  Returns DL_EINVAL for another kind or a null cfg.
  */
 int dl_profile_config(int32_t kind, int32_t *cfg);

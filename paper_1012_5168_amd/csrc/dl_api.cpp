@@ -323,6 +323,16 @@ ProfScope::~ProfScope()
     }
 }
 
+void prof_config(int kind, int kind2, const TuneChoice &t)
+{
+    std::lock_guard<std::mutex> lk(g_prof_mu);
+    for (int k : {kind, kind2})
+        if (k >= 0 && k < PROF_NKIND) {
+            g_prof_cfg[k] = t;
+            g_prof_cfg_set[k] = true;
+        }
+}
+
 static void prof_drain_locked()
 {
     std::vector<unsigned> ctr;
@@ -423,14 +433,9 @@ std::vector<int> launch_dslash_batch(const std::vector<DslashCall> &c0, hipStrea
     }
     ps.bytes = nominal;
     if (counted) {
-        std::lock_guard<std::mutex> lk(g_prof_mu);
         TuneChoice used = t;
         if (t.kind == 1 && !dslash_lds_ok(c[0].prec, c[0].recon)) used = TuneChoice{0, 1, 256, 0};
-        for (int k : {ps.kind, ps.kind2})
-            if (k >= 0 && k < PROF_NKIND) {
-                g_prof_cfg[k] = used;
-                g_prof_cfg_set[k] = true;
-            }
+        prof_config(ps.kind, ps.kind2, used);
     }
     launch_dslash_any(c, t, s);
     return nblk;
@@ -669,14 +674,13 @@ bool schur_op(int op) { return op == DL_OP_MHAT || op == DL_OP_MHATDAG; }
 
 // The launches of dl_apply on packed parity fields: ie / io receive the packed
 // input, oe / oo the output, tmp (Schur operators only) the odd-site
-// intermediate.  Every field is written before it is read; the odd output of
-// a Schur operator is cleared.
+// intermediate.  Every field is written before it is read; a Schur operator
+// neither reads io nor writes oo, and clears the odd sites of the output.
 void apply_op(const Ctx &c, int op, int prec, double kappa, const void *in, void *out, int n, Field ie, Field io,
               Field oe, Field oo, Field tmp)
 {
-    const int64_t Vh = c.G->lat.Vh;
-    k_pack(prec, ie, 0, static_cast<const double *>(in), c.g, n, c.s);
-    k_pack(prec, io, 1, static_cast<const double *>(in), c.g, n, c.s);
+    const bool schur = schur_op(op);
+    k_pack(prec, ie, schur ? NOF : io, static_cast<const double *>(in), c.g, n, c.s);
     const bool dag = op == DL_OP_MDAG || op == DL_OP_MHATDAG || op == DL_OP_DHOPDAG;
     switch (op) {
     case DL_OP_DHOP:
@@ -692,11 +696,23 @@ void apply_op(const Ctx &c, int op, int prec, double kappa, const void *in, void
     default:  // Schur complement on even sites
         launch_dslash(dcall(c, prec, 1, dag, EPI_PLAIN, ie, tmp, NOF, NOF, 1.0, n, nullptr, nullptr), c.s);
         launch_dslash(dcall(c, prec, 0, dag, EPI_XPAY, tmp, oe, ie, NOF, -kappa * kappa, n, nullptr, nullptr), c.s);
-        vec_launch(V_ZERO, prec, {VSeg{{oo, NOF, NOF, NOF, NOF}, nullptr, nullptr, Vh, n, nullptr}}, c.s);
         break;
     }
-    k_unpack(prec, oe, 0, static_cast<double *>(out), c.g, n, c.s);
-    k_unpack(prec, oo, 1, static_cast<double *>(out), c.g, n, c.s);
+    k_unpack(prec, oe, schur ? NOF : oo, static_cast<double *>(out), c.g, n, c.s);
+    DL_HIP(hipGetLastError());
+}
+
+// The operators that k_canon_op applies to canonical FP64 fields as they are.
+bool canon_op(const Ctx &c, int op, int prec)
+{
+    return prec == P64 && !schur_op(op) && canon_op_fits(c.g);
+}
+
+void apply_canon(const Ctx &c, int op, double kappa, const void *in, void *out, int n)
+{
+    const bool xpay = op == DL_OP_M || op == DL_OP_MDAG;
+    k_canon_op(c.links(P64), c.G->recon, op == DL_OP_MDAG || op == DL_OP_DHOPDAG, xpay, xpay ? -kappa : 1.0, in, out,
+               c.g, n, c.s);
     DL_HIP(hipGetLastError());
 }
 
@@ -711,12 +727,20 @@ extern "C" int dl_apply(dl_gauge G, double kappa, int32_t op, int32_t prec, cons
         Ctx c{G, G->lat.geom(), static_cast<hipStream_t>(stream)};
         const int n = (int)nrhs;
         const int64_t Vh = G->lat.Vh;
+        if (canon_op(c, op, prec)) {
+            apply_canon(c, op, kappa, in, out, n);
+            DL_HIP(hipStreamSynchronize(c.s));
+            return DL_OK;
+        }
         HalfField ie, io, oe, oo, tmp;
         ie.alloc(prec, n, Vh);
-        io.alloc(prec, n, Vh);
         oe.alloc(prec, n, Vh);
-        oo.alloc(prec, n, Vh);
-        if (schur_op(op)) tmp.alloc(prec, n, Vh);
+        if (schur_op(op)) {
+            tmp.alloc(prec, n, Vh);
+        } else {
+            io.alloc(prec, n, Vh);
+            oo.alloc(prec, n, Vh);
+        }
         apply_op(c, op, prec, kappa, in, out, n, ie.view(), io.view(), oe.view(), oo.view(), tmp.view());
         DL_HIP(hipStreamSynchronize(c.s));
         return DL_OK;
@@ -796,7 +820,10 @@ extern "C" int dl_apply_noalloc(dl_gauge G, double kappa, int32_t op, int32_t pr
               oo = carve(p, prec, n, Vh);
         Field tmp = schur_op(op) ? carve(p, prec, n, Vh) : NOF;
         Ctx c{G, G->lat.geom(), static_cast<hipStream_t>(stream)};
-        apply_op(c, op, prec, kappa, in, out, n, ie, io, oe, oo, tmp);
+        if (canon_op(c, op, prec))
+            apply_canon(c, op, kappa, in, out, n);
+        else
+            apply_op(c, op, prec, kappa, in, out, n, ie, io, oe, oo, tmp);
         return DL_OK;
     });
 }
@@ -1468,19 +1495,15 @@ extern "C" int dl_solve(dl_gauge G, double kappa, const dl_solve_params *params,
             std::vector<double> res2;
             if (cg) {
                 w.alloc_cgnr(prm.prec, n, Vh);
-                k_pack(prm.prec, w.be.view(), 0, bsrc, c.g, n, c.s);
-                k_pack(prm.prec, w.bo.view(), 1, bsrc, c.g, n, c.s);
+                k_pack(prm.prec, w.be.view(), w.bo.view(), bsrc, c.g, n, c.s);
                 cgnr_batch(c, kappa, prm.fixed_iters, w);
-                k_unpack(prm.prec, w.x64.view(), 0, xdst, c.g, n, c.s);
-                k_unpack(prm.prec, w.xo.view(), 1, xdst, c.g, n, c.s);
+                k_unpack(prm.prec, w.x64.view(), w.xo.view(), xdst, c.g, n, c.s);
             } else {
                 w.alloc_bicg(prm.prec, n, Vh);
-                k_pack(P64, w.be.view(), 0, bsrc, c.g, n, c.s);
-                k_pack(P64, w.bo.view(), 1, bsrc, c.g, n, c.s);
+                k_pack(P64, w.be.view(), w.bo.view(), bsrc, c.g, n, c.s);
                 bicgstab_batch(c, kappa, prm, w);
                 true_residual_full(c, kappa, w, res2);
-                k_unpack(P64, w.x64.view(), 0, xdst, c.g, n, c.s);
-                k_unpack(P64, w.xo.view(), 1, xdst, c.g, n, c.s);
+                k_unpack(P64, w.x64.view(), w.xo.view(), xdst, c.g, n, c.s);
             }
             DL_HIP(hipGetLastError());
             DL_HIP(hipStreamSynchronize(c.s));
@@ -1579,8 +1602,7 @@ extern "C" int dl_sources_fill(dl_lattice lat, const dl_sources *src, int64_t fi
         fo.alloc(P64, n, lat->Vh);
         k_source(P64, fe.view(), 0, ss, g, n, s);
         k_source(P64, fo.view(), 1, ss, g, n, s);
-        k_unpack(P64, fe.view(), 0, static_cast<double *>(out), g, n, s);
-        k_unpack(P64, fo.view(), 1, static_cast<double *>(out), g, n, s);
+        k_unpack(P64, fe.view(), fo.view(), static_cast<double *>(out), g, n, s);
         DL_HIP(hipGetLastError());
         DL_HIP(hipStreamSynchronize(s));
         return DL_OK;
@@ -1872,16 +1894,14 @@ extern "C" int dl_smear(dl_gauge G, double alpha, int32_t iters, const void *in,
         ao.alloc(P64, n, Vh);
         be.alloc(P64, n, Vh);
         bo.alloc(P64, n, Vh);
-        k_pack(P64, ae.view(), 0, static_cast<const double *>(in), c.g, n, c.s);
-        k_pack(P64, ao.view(), 1, static_cast<const double *>(in), c.g, n, c.s);
+        k_pack(P64, ae.view(), ao.view(), static_cast<const double *>(in), c.g, n, c.s);
         HalfField *pe = &ae, *po = &ao, *qe = &be, *qo = &bo;
         for (int it = 0; it < iters; ++it) {
             k_smear(c.links(P64), G->recon, pe->view(), po->view(), qe->view(), qo->view(), c.g, n, alpha, c.s);
             std::swap(pe, qe);
             std::swap(po, qo);
         }
-        k_unpack(P64, pe->view(), 0, static_cast<double *>(out), c.g, n, c.s);
-        k_unpack(P64, po->view(), 1, static_cast<double *>(out), c.g, n, c.s);
+        k_unpack(P64, pe->view(), po->view(), static_cast<double *>(out), c.g, n, c.s);
         DL_HIP(hipGetLastError());
         DL_HIP(hipStreamSynchronize(c.s));
         return DL_OK;

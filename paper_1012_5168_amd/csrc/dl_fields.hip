@@ -1,7 +1,6 @@
-// dl_fields.hip -- layout conversion (canonical <-> even-odd SoA, and the
-// chiral spin basis <-> the stored basis of dl_common.hpp), noise and point
-// sources with dilution masks, the timeslice trace reduction and the gamma
-// contraction of the loops, and link-format conversion.
+// dl_fields.hip -- noise and point sources with dilution masks, the timeslice
+// trace reduction and the gamma contraction of the loops, smearing, the link
+// gradient, and link-format conversion.
 #include "dl_dslash.hpp"
 
 namespace dl {
@@ -75,46 +74,6 @@ __device__ __forceinline__ void source_site(const SourceSpec &src, int rhs, cons
 }
 
 // ---------------------------------------------------------------- kernels
-
-template <typename S>
-__global__ __launch_bounds__(BS) void pack_kernel(Field dst, int parity, const double *canon, Geom g)
-{
-    using R = typename Fmt<S>::R;
-    const int rhs = blockIdx.y;
-    const int cb = blockIdx.x * BS + threadIdx.x;
-    if (cb >= g.Vh) return;
-    const Site s = decode(g, cb, parity);
-    const int64_t V = 2 * (int64_t)g.Vh;
-    const double2 *src = reinterpret_cast<const double2 *>(canon) + ((int64_t)rhs * V + lex_index(g, s)) * 12;
-    cx<double> z[12];
-#pragma unroll
-    for (int e = 0; e < 12; ++e) z[e] = {src[e].x, src[e].y};
-    to_internal(z);
-    cx<R> v[12];
-#pragma unroll
-    for (int e = 0; e < 12; ++e) v[e] = {R(z[e].re), R(z[e].im)};
-    store_spinor<S>(dst, g.Vh, rhs, cb, v);
-}
-
-template <typename S>
-__global__ __launch_bounds__(BS) void unpack_kernel(Field src, int parity, double *canon, Geom g)
-{
-    using R = typename Fmt<S>::R;
-    const int rhs = blockIdx.y;
-    const int cb = blockIdx.x * BS + threadIdx.x;
-    if (cb >= g.Vh) return;
-    const Site s = decode(g, cb, parity);
-    const int64_t V = 2 * (int64_t)g.Vh;
-    double2 *dst = reinterpret_cast<double2 *>(canon) + ((int64_t)rhs * V + lex_index(g, s)) * 12;
-    cx<R> v[12];
-    load_spinor<S>(src, g.Vh, rhs, cb, v);
-    cx<double> z[12];
-#pragma unroll
-    for (int e = 0; e < 12; ++e) z[e] = {(double)v[e].re, (double)v[e].im};
-    to_canonical(z);
-#pragma unroll
-    for (int e = 0; e < 12; ++e) dst[e] = make_double2(z[e].re, z[e].im);
-}
 
 template <typename S>
 __global__ __launch_bounds__(BS) void source_kernel(Field dst, int parity, SourceSpec src, Geom g)
@@ -499,18 +458,6 @@ double field_bytes(int prec, int64_t Vh, int nrhs)
 }
 
 }  // namespace
-
-void k_pack(int prec, Field dst, int parity, const double *canon, const Geom &g, int nrhs, hipStream_t s)
-{
-    dim3 grid((g.Vh + BS - 1) / BS, nrhs);
-    DL_DISPATCH(prec, pack_kernel, grid, dim3(BS), 0, s, dst, parity, canon, g);
-}
-
-void k_unpack(int prec, Field src, int parity, double *canon, const Geom &g, int nrhs, hipStream_t s)
-{
-    dim3 grid((g.Vh + BS - 1) / BS, nrhs);
-    DL_DISPATCH(prec, unpack_kernel, grid, dim3(BS), 0, s, src, parity, canon, g);
-}
 
 void k_source(int prec, Field dst, int parity, const SourceSpec &src, const Geom &g, int nrhs, hipStream_t s)
 {

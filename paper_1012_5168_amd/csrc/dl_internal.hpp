@@ -206,6 +206,7 @@ std::vector<int> launch_dslash_batch(const std::vector<DslashCall> &calls, hipSt
 struct TuneChoice {
     int kind, nr, bs, persistent;
 };
+void prof_config(int kind, int kind2, const TuneChoice &t);  // the last profiled launch's configuration
 TuneChoice tune_lookup(const std::vector<DslashCall> &c, hipStream_t s);
 void launch_dslash_any(const std::vector<DslashCall> &c, const TuneChoice &t, hipStream_t s);
 // whether the LDS-link kernel serves this precision and link format (its
@@ -312,9 +313,14 @@ void scalar_launch(int op, const std::vector<SSeg> &segs, const SParams &p, hipS
 
 // ---------------------------------------------------------------- fields, sources, traces
 
-// canonical complex128 [nrhs][V][4][3] <-> parity fields
-void k_pack(int prec, Field dst, int parity, const double *canon, const Geom &g, int nrhs, hipStream_t s);
-void k_unpack(int prec, Field src, int parity, double *canon, const Geom &g, int nrhs, hipStream_t s);
+// canonical complex128 [nrhs][V][4][3] <-> parity fields (odd with null data: the even sites only, zeros written to the
+// odd ones)
+void k_pack(int prec, Field even, Field odd, const double *canon, const Geom &g, int nrhs, hipStream_t s);
+void k_unpack(int prec, Field even, Field odd, double *canon, const Geom &g, int nrhs, hipStream_t s);
+// out = a D in (or in + a D in, xpay) on canonical FP64 fields; D^+ with dag
+bool canon_op_fits(const Geom &g);
+void k_canon_op(const void *links, int recon, bool dag, bool xpay, double a, const void *in, void *out, const Geom &g,
+                int nrhs, hipStream_t s);
 
 // internal source kind: the source is a stored FP64 field pair (xe, xo), e.g.
 // a smeared noise, instead of being regenerated from the counter stream

@@ -50,3 +50,43 @@ def test_solve_around_the_partial_sums_split(dl, dev, dims, prec):
     for r in range(2):
         assert st[r][0] == dl.DL_OK and st[r][3] <= 1e-10, st[r]
         assert oracle_residual(U, x[r], b[r], dims, kappa) <= 1.5e-10
+
+
+# rows of 8 sites (a divisor of the 64-site tiles: x neighbours inside the tile) and of 6 and 10, last tiles of 64, 32
+# and 16 sites; one right-hand side per wavefront up to 68 / 89 / 60 of them, several above
+@pytest.mark.parametrize("dims,nrhs", [((8, 6, 4, 10), 1), ((8, 6, 4, 10), 70), ((6, 4, 6, 10), 2), ((6, 4, 6, 10), 91),
+                                       ((10, 6, 4, 8), 3), ((2, 2, 2, 2), 5), ((4, 2, 6, 4), 1)])
+@pytest.mark.parametrize("recon", [12, 18])
+def test_operators_on_canonical_fields(dl, dev, dims, nrhs, recon):
+    U = synth.gauge_field(dims, 0.6, seed=911)
+    kappa = 0.131
+    psi = synth.random_spinor(dims, nrhs, seed=912)
+    x = to_dev(psi, dev)
+    for tap in (1, 0):
+        G = dl.Gauge(dl.Lattice(dims, tap), U, recon=recon)
+        for op in (dl.DL_OP_DHOP, dl.DL_OP_DHOPDAG, dl.DL_OP_M, dl.DL_OP_MDAG):
+            out = from_dev(dl.apply(G, kappa, op, x))
+            dag = op in (dl.DL_OP_DHOPDAG, dl.DL_OP_MDAG)
+            for r in {0, nrhs // 2, nrhs - 1}:
+                ref = oracle.dhop(U, psi[r], dims, tap, dag=dag)
+                if op in (dl.DL_OP_M, dl.DL_OP_MDAG):
+                    ref = psi[r] - kappa * ref
+                assert np.max(np.abs(out[r] - ref)) <= 1e-13 * np.max(np.abs(ref)), (tap, op, r)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 6, 10), (16, 4, 4, 6)])
+def test_pack_and_unpack_keep_the_bits(dl, dev, dims):
+    """FP64 solves with kappa = 0 return their source, through both conversions, bit for bit in the canonical basis
+    where the entries are unit sources or complex Z2; the Schur operator at kappa = 0 returns the even sites and
+    clears the odd ones."""
+    U = synth.gauge_field(dims, 0.4, seed=921)
+    G = dl.Gauge(dl.Lattice(dims, 1), U)
+    V = int(np.prod(dims))
+    src = dl.z2_sources(77, 3)
+    b = torch.empty((3, V, 4, 3), dtype=torch.complex128, device=dev)
+    dl.dl_sources_fill(G.lattice.h, src, 0, 3, b)
+    ref = np.stack([oracle.z2_source(dims, 77, n, 0, 0) for n in range(3)])
+    assert np.array_equal(from_dev(b), ref)
+    out = from_dev(dl.apply(G, 0.0, dl.DL_OP_MHAT, b))
+    even = oracle.parity(dims) == 0
+    assert np.array_equal(out[:, even], ref[:, even]) and not out[:, ~even].any()
