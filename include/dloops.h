@@ -467,7 +467,7 @@ uint64_t dl_cache_bytes(void);
  * links once per launch plus the in/out/epilogue half spinors of each live
  * right-hand side).  kind: 0 = all hopping kernels, 1 = Krylov vector
  * kernels, 2 = sources and traces, 3 = the plain (no epilogue, not adjoint)
- * hopping kernel, 4 = smearing steps.  Returns DL_EINVAL for another kind.
+ * hopping kernel, 4 = smearing.  Returns DL_EINVAL for another kind.
  */
 int dl_profile_enable(int32_t on);
 int64_t dl_profile_read(int32_t kind, double *ms, double *bytes);

@@ -1715,16 +1715,21 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
         if (smear_iters > 0) {
             xe.alloc(P64, n, Vh);
             xo.alloc(P64, n, Vh);
-            te.alloc(P64, n, Vh);
-            to.alloc(P64, n, Vh);
             k_source(P64, xe.view(), 0, ss, c.g, n, c.s);
             k_source(P64, xo.view(), 1, ss, c.g, n, c.s);
             HalfField *ae = &xe, *ao = &xo, *be = &te, *bo = &to;
-            for (int it = 0; it < smear_iters; ++it) {
-                k_smear(c.links(P64), G->recon, ae->view(), ao->view(), be->view(), bo->view(), c.g, n, smear_alpha,
-                        c.s);
-                std::swap(ae, be);
-                std::swap(ao, bo);
+            if (smear_chip_fits(c.g, n)) {
+                k_smear_chip(c.links(P64), G->recon, SmearIO{{xe.data.p, xo.data.p}, {xe.data.p, xo.data.p}}, false,
+                             c.g, n, smear_alpha, smear_iters, c.s);
+            } else {
+                te.alloc(P64, n, Vh);
+                to.alloc(P64, n, Vh);
+                for (int it = 0; it < smear_iters; ++it) {
+                    k_smear(c.links(P64), G->recon, ae->view(), ao->view(), be->view(), bo->view(), c.g, n,
+                            smear_alpha, c.s);
+                    std::swap(ae, be);
+                    std::swap(ao, bo);
+                }
             }
             sx.kind = SRC_STORED;
             sx.xe = ae->view();
@@ -1886,6 +1891,13 @@ extern "C" int dl_smear(dl_gauge G, double alpha, int32_t iters, const void *in,
         if (iters == 0) {
             // S = 1: the output is the input, bit for bit
             DL_HIP(hipMemcpyAsync(out, in, (size_t)n * G->lat.V * 24 * sizeof(double), hipMemcpyDeviceToDevice, c.s));
+            DL_HIP(hipStreamSynchronize(c.s));
+            return DL_OK;
+        }
+        if (smear_chip_fits(c.g, n)) {
+            k_smear_chip(c.links(P64), G->recon, SmearIO{{in, nullptr}, {out, nullptr}}, true, c.g, n, alpha, iters,
+                         c.s);
+            DL_HIP(hipGetLastError());
             DL_HIP(hipStreamSynchronize(c.s));
             return DL_OK;
         }

@@ -226,6 +226,205 @@ __global__ __launch_bounds__(BS) void smear_kernel(const void *links, Field in_s
     store_spinor<double>(out, g.Vh, rhs, cb, x);
 }
 
+// All steps of the smearing at once, where a timeslice fits on a CU.  F couples
+// neither timeslices nor spins, so the three colours of one spin on one
+// timeslice of one field are a problem of their own (48 bytes a site, 192 KiB
+// at 16^3): a workgroup reads it once, keeps it in registers (K sites of each
+// parity per thread) and takes every step there, the neighbours' colours
+// passing through LDS one parity at a time (an even site's neighbours are
+// odd), and writes it once.  The fields then cross memory once per call
+// instead of three times per step; what is left per step is the links, which
+// the problems of one timeslice, all on one XCD, read from its L2: 576 bytes a
+// site and step through a CU's 64-byte-per-clock load path, which bounds it.
+// Measured, 10 steps on 24 fields at 16^3 x 32: 6.03 -> 3.22 ms (step by step
+// through memory, with the conversions, before); 26 us per step and round of
+// 256 problems, of which the FP64 arithmetic (a third of it the links' third
+// rows) is 16 and the links' loads 15.  20 steps on 48 fields: 8^3 x 16 1280 ->
+// 747 us, 6^3 x 12 670 -> 300; on one field 16^3 x 32 603 -> 484, 4^3 x 8 277 ->
+// 74.  Sixteen wavefronts of two sites instead of eight of four took 4.48 ms
+// (no registers to load a link ahead); holding the links in registers where one
+// site per thread leaves room gained nothing.
+template <int NE, int NT, int K, bool CANON>
+__global__ __launch_bounds__(NT) void smear_chip_kernel(const void *links, SmearIO io, Geom g, double alpha, double norm,
+                                                        int iters, int nrhs)
+{
+    using D2 = double __attribute__((ext_vector_type(2)));
+    extern __shared__ D2 ex[];  // [3 colours][H] of one parity
+    const int H = g.sT;         // checkerboard sites of a timeslice and parity
+    // items (t, rhs, spin), spin fastest; XCD x takes a contiguous eighth of them
+    const int64_t total = gridDim.x;
+    const int xcd = blockIdx.x % 8;
+    const int64_t item = xcd * (total / 8) + min<int64_t>(xcd, total % 8) + blockIdx.x / 8;
+    const int spin = (int)(item & 3), rhs = (int)((item >> 2) % nrhs), t = (int)((item >> 2) / nrhs);
+    const int64_t t0 = (int64_t)t * H;
+    int nb[2][K][3];  // neighbours in the other parity's order, two 16-bit indices each: x+ | x-, y+ | y-, z+ | z-
+    cx<double> v[2][K][3];
+    // checkerboard site j of parity p on this timeslice
+    struct Place {
+        int kx, y, z, odd;
+    };
+    auto place = [&](int p, int j) {
+        const int row = j / g.Xh, z = row / g.Y, y = row - z * g.Y;
+        return Place{j - row * g.Xh, y, z, (p + y + z + t) & 1};
+    };
+    // its three colours in a field: first word and distance (canonical: 12 words a site, site
+    // 2 (t0 + j) + odd; packed: a plane per component)
+    auto words = [&](const void *const f[2], int p, int j) {
+        if constexpr (CANON)
+            return static_cast<const D2 *>(f[0]) +
+                   (((int64_t)rhs * 2 * g.Vh + 2 * (t0 + j) + place(p, j).odd) * 12 + 3 * spin);
+        else
+            return reinterpret_cast<const D2 *>(static_cast<const char *>(f[p]) + rhs * rhs_stride_bytes(g.Vh, 16)) +
+                   (3 * spin * plane_stride(g.Vh) + t0 + j);
+    };
+    const int64_t apart = CANON ? 1 : plane_stride(g.Vh);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = min((int)threadIdx.x + k * NT, H - 1);
+            const Place a = place(p, j);
+            const int xp = a.odd ? (a.kx + 1 == g.Xh ? 0 : a.kx + 1) : a.kx;
+            const int xm = a.odd ? a.kx : (a.kx == 0 ? g.Xh - 1 : a.kx - 1);
+            const int yp = a.y + 1 == g.Y ? j - (g.Y - 1) * g.sY : j + g.sY;
+            const int ym = a.y == 0 ? j + (g.Y - 1) * g.sY : j - g.sY;
+            const int zp = a.z + 1 == g.Z ? j - (g.Z - 1) * g.sZ : j + g.sZ;
+            const int zm = a.z == 0 ? j + (g.Z - 1) * g.sZ : j - g.sZ;
+            nb[p][k][0] = (j - a.kx + xp) | (j - a.kx + xm) << 16;
+            nb[p][k][1] = yp | ym << 16;
+            nb[p][k][2] = zp | zm << 16;
+            const D2 *src = words(io.in, p, j);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const D2 w = src[c * apart];
+                v[p][k][c] = {w.x, w.y};
+            }
+        }
+    // the exchange buffer <- parity p, and back
+    auto put = [&](int p) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = threadIdx.x + k * NT;
+            if (j < H)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) ex[c * H + j] = D2{v[p][k][c].re, v[p][k][c].im};
+        }
+    };
+    auto get = [&](int p) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = min((int)threadIdx.x + k * NT, H - 1);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const D2 w = ex[c * H + j];
+                v[p][k][c] = {w.x, w.y};
+            }
+        }
+    };
+    // the stored rows of the link of direction d at site k of parity p
+    auto link = [&](int p, int k, int d, cx<double> u[NE]) {
+        const bool fwd = (d & 1) == 0;
+        int l = fwd ? min((int)threadIdx.x + k * NT, H - 1) : nb[p][k][d >> 1] >> 16;
+        asm volatile("" : "+v"(l)::"memory");
+        const D2 *q = static_cast<const D2 *>(links) + (int64_t)((d >> 1) * 2 + (fwd ? p : 1 - p)) * NE * g.Vh + t0 + l;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const D2 z = q[e * (int64_t)g.Vh];
+            u[e] = {z.x, z.y};
+        }
+    };
+    cx<double> un[2][NE];
+    link(0, 0, 0, un[0]);
+    // one step of site k of parity p, its neighbours' old values in the buffer
+    auto step = [&](int p, int k, cx<double> o[3]) {
+        cx<double> acc[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] = {0.0, 0.0};
+        // The links do not change from step to step, but the compiler must not lift their loads
+        // out of the steps (everything spills): they are loaded a direction ahead, the next
+        // site's first with this one's last, and fences keep the loads of further directions
+        // behind the arithmetic.
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            const bool fwd = (d & 1) == 0;
+            if (d < 5)
+                link(p, k, d + 1, un[(d + 1) & 1]);
+            else if (k + 1 < K)
+                link(p, k + 1, 0, un[0]);
+            else
+                link(1 - p, 0, 0, un[0]);
+            int n = fwd ? nb[p][k][d >> 1] & 0xffff : nb[p][k][d >> 1] >> 16;
+            asm volatile("" : "+v"(n)::"memory");
+            cx<double> u[9], w[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const D2 z = ex[c * H + n];
+                w[c] = {z.x, z.y};
+            }
+#pragma unroll
+            for (int e = 0; e < NE; ++e) u[e] = un[d & 1][e];
+            if constexpr (NE == 6) {
+                u[6] = conj(u[1] * u[5] - u[2] * u[4]);
+                u[7] = conj(u[2] * u[3] - u[0] * u[5]);
+                u[8] = conj(u[0] * u[4] - u[1] * u[3]);
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    if (fwd)
+                        cmac(acc[i], u[3 * i + c], w[c]);
+                    else
+                        cmac_conj(acc[i], u[3 * c + i], w[c]);
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(acc[c].re), "+v"(acc[c].im)::"memory");
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            o[c].re = norm * fma(alpha, acc[c].re, v[p][k][c].re);
+            o[c].im = norm * fma(alpha, acc[c].im, v[p][k][c].im);
+        }
+    };
+    for (int it = 0; it < iters; ++it) {
+        cx<double> o[K][3];
+        // even sites from the odd ones, which only the buffer holds meanwhile
+        put(1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) step(0, k, o[k]);
+        get(1);
+        __syncthreads();
+        put(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[0][k][c] = o[k][c];
+        __syncthreads();
+        // odd sites from the old even ones
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            step(1, k, o[k]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[1][k][c] = o[k][c];
+        }
+        __syncthreads();
+    }
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // the places anew, rather than kept over the steps
+    const void *const to[2] = {io.out[0], io.out[1]};
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = tid + k * NT;
+            if (j >= H) continue;
+            D2 *dst = const_cast<D2 *>(words(to, p, j));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dst[c * apart] = D2{v[p][k][c].re, v[p][k][c].im};
+        }
+}
+
 // Disconnected two-loop correlator (Section 3, Eq. 2) from per-noise loops
 // l[n][T] complex (re, im interleaved).  noise_sum_kernel: sum[t] = sum_n l[n][t]
 // (one thread per t, n in order).  corr_kernel, block dt: the ordered pairs of
@@ -508,6 +707,55 @@ void k_smear(const void *links, int recon, Field ine, Field ino, Field oute, Fie
             hipLaunchKernelGGL(smear_kernel<9>, grid, dim3(BS), 0, s, links, sub(ino), sub(ine), sub(outo), 1, g,
                                alpha, norm, n);
         }
+    }
+}
+
+// Whether smear_chip_kernel takes a field: up to two sites of each parity per
+// thread (three would not leave the registers of 1024 threads room for a step),
+// 96 KiB of LDS, and a grid of (timeslice, field, spin) problems below 2^31.
+bool smear_chip_fits(const Geom &g, int nrhs) { return g.sT <= 2048 && 4LL * g.T * nrhs < (1LL << 31); }
+
+template <int NE, bool CANON>
+static void smear_chip_go(const void *links, const SmearIO &io, const Geom &g, int nrhs, double alpha, int iters,
+                          hipStream_t s)
+{
+    const double norm = 1.0 / (1.0 + 6.0 * alpha);
+    const dim3 grid(4u * g.T * nrhs);
+    const size_t lds = (size_t)3 * g.sT * 16;
+    auto go = [&](auto kernel, int nt) {
+        DL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   3 * 2048 * 16));
+        hipLaunchKernelGGL(kernel, grid, dim3(nt), lds, s, links, io, g, alpha, norm, iters, nrhs);
+    };
+    if (g.sT <= 64)
+        go(smear_chip_kernel<NE, 64, 1, CANON>, 64);
+    else if (g.sT <= 128)
+        go(smear_chip_kernel<NE, 128, 1, CANON>, 128);
+    else if (g.sT <= 256)
+        go(smear_chip_kernel<NE, 256, 1, CANON>, 256);
+    else if (g.sT <= 512)
+        go(smear_chip_kernel<NE, 512, 1, CANON>, 512);
+    else if (g.sT <= 1024)
+        go(smear_chip_kernel<NE, 512, 2, CANON>, 512);
+    else
+        go(smear_chip_kernel<NE, 512, 4, CANON>, 512);
+}
+
+void k_smear_chip(const void *links, int recon, const SmearIO &io, bool canon, const Geom &g, int nrhs, double alpha,
+                  int iters, hipStream_t s)
+{
+    // the fields once in and once out, and the links of the three spatial directions once
+    ProfScope ps(PROF_SMEAR, 4 * field_bytes(P64, g.Vh, nrhs) + 2.0 * 3 * g.Vh * (recon == 12 ? 6 : 9) * 16, s);
+    if (recon == 12) {
+        if (canon)
+            smear_chip_go<6, true>(links, io, g, nrhs, alpha, iters, s);
+        else
+            smear_chip_go<6, false>(links, io, g, nrhs, alpha, iters, s);
+    } else {
+        if (canon)
+            smear_chip_go<9, true>(links, io, g, nrhs, alpha, iters, s);
+        else
+            smear_chip_go<9, false>(links, io, g, nrhs, alpha, iters, s);
     }
 }
 

@@ -347,6 +347,15 @@ void k_trace(int prec, Field se, Field so, const SourceSpec &src, const Geom &g,
 // spatial, spin-diagonal hopping term; in and out must not overlap
 void k_smear(const void *links, int recon, Field ine, Field ino, Field oute, Field outo, const Geom &g, int nrhs,
              double alpha, hipStream_t s);
+// All `iters` (>= 1) steps in one launch, where a timeslice fits on a CU (smear_chip_fits): in and out are canonical
+// fields (in[0], out[0]) or the data of packed parity fields; in and out may be the same memory.
+struct SmearIO {
+    const void *in[2];
+    void *out[2];
+};
+bool smear_chip_fits(const Geom &g, int nrhs);
+void k_smear_chip(const void *links, int recon, const SmearIO &io, bool canon, const Geom &g, int nrhs, double alpha,
+                  int iters, hipStream_t s);
 // disconnected correlator: out[dt] = -norm * sum over distinct noise pairs (sb, sa: [T] complex scratch)
 // Eqs. 3-4 (dl_fit.cpp): the flavour-singlet combination and the ratio fit
 void eta_prime_fit(const double *d, const double *c, int ncfg, int T, double m_pi, int tmin, int tmax, double *c_eta,

@@ -90,3 +90,38 @@ def test_pack_and_unpack_keep_the_bits(dl, dev, dims):
     out = from_dev(dl.apply(G, 0.0, dl.DL_OP_MHAT, b))
     even = oracle.parity(dims) == 0
     assert np.array_equal(out[:, even], ref[:, even]) and not out[:, ~even].any()
+
+
+# timeslices of 64, 72, 256, 384, 864, 1536, 2048 and 2304 sites per parity: one to sixteen wavefronts with one or two
+# sites of each parity per thread, full and ragged, and the first size that goes step by step through memory
+SMEAR_DIMS = [(4, 4, 8, 4), (6, 4, 6, 2), (8, 8, 8, 2), (8, 8, 12, 2), (12, 12, 12, 2), (16, 16, 12, 2), (16, 16, 16, 2),
+              (16, 16, 18, 2)]
+
+
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims", SMEAR_DIMS)
+def test_smearing_of_given_fields(dl, dev, dims, recon):
+    U = synth.gauge_field(dims, 0.6, seed=931)
+    G = dl.Gauge(dl.Lattice(dims, 1), U, recon=recon)
+    psi = synth.random_spinor(dims, 3, seed=932)
+    for alpha, iters in ((0.5, 4), (0.0, 1)):
+        out = from_dev(dl.smear(G, alpha, iters, to_dev(psi, dev)))
+        for r in range(3):
+            ref = oracle.smear(U, psi[r], dims, alpha, iters)
+            assert np.max(np.abs(out[r] - ref)) <= 1e-13 * np.max(np.abs(ref)), (alpha, iters, r)
+
+
+@pytest.mark.parametrize("dims", SMEAR_DIMS[:1] + SMEAR_DIMS[3:6])
+def test_smearing_of_the_sources_of_a_loop(dl, dev, dims):
+    """Through the packed fields of the solver: two CGNR iterations, then the trace with the smeared noise."""
+    U = synth.gauge_field(dims, 0.5, seed=941)
+    kappa, alpha, iters = 0.12, 0.4, 3
+    G = dl.Gauge(dl.Lattice(dims, 1), U)
+    prm = dl.solve_params(solver=dl.DL_CGNR, fixed_iters=2)
+    L, _ = dl.loops_smeared(G, kappa, dl.z2_sources(942, 2), alpha, iters, [0, 15], prm)
+    for n in range(2):
+        xi = oracle.smear(U, oracle.z2_source(dims, 942, n), dims, alpha, iters)
+        s = oracle.solve_lp(U, xi, dims, kappa, niter=2)
+        ref = oracle.loops_accumulate(dims, xi, s, [0, 15])
+        scale = np.linalg.norm(xi.reshape(dims[3], -1), axis=1) * np.linalg.norm(s.reshape(dims[3], -1), axis=1)
+        assert np.max(np.abs(L[n] - ref) / scale) < 1e-12, n
