@@ -846,6 +846,7 @@ struct SolveWork {
     int *upd() const { return flags.as<int>() + n; }
     int *restart() const { return flags.as<int>() + 2 * n; }
     int nblk_max = 0;
+    bool res2_known = false;  // parts2 holds the full-lattice residuals of the last solve (small_solve)
 
     void alloc_bicg(int prec_, int n_, int64_t Vh)
     {
@@ -1148,6 +1149,70 @@ bool fault_injected(const char *where)
     return e != nullptr && std::strcmp(e, where) == 0;
 }
 
+// Lattices of at most SMALL_VH sites per parity in FP64 or FP32: one kernel per
+// problem instead of the launches below (the 16-bit formats order a spinor's
+// components differently and take the general path).  With use_graph the
+// kernels, the whole solve, are what is captured and replayed.
+bool small_solve(const std::vector<Prob> &P, const dl_solve_params &prm, hipStream_t user_stream)
+{
+    const int prec = P[0].w->prec;
+    for (const Prob &p : P) p.w->res2_known = false;
+    if (prec != P64 && prec != P32) return false;
+    for (const Prob &p : P)
+        if (p.Vh() > SMALL_VH) return false;
+    const double delta = prec == P64 ? 0.0 : prm.delta > 0 ? prm.delta : 0.01;
+    std::vector<SmallArgs> args;
+    for (const Prob &p : P) {
+        SolveWork &w = *p.w;
+        SmallArgs A;
+        A.g = p.c.g;
+        A.be = w.be.view();
+        A.bo = w.bo.view();
+        A.bhat = w.bhat.view();
+        A.x64 = w.x64.view();
+        A.xo = w.xo.view();
+        A.r = w.r.view();
+        A.rh = w.rh.view();
+        A.p = w.p.view();
+        A.v = w.v.view();
+        A.t = w.t.view();
+        A.mid = w.tmpo.view();
+        A.mid64 = w.tmp64.view();
+        A.xlo = prec == P64 ? NOF : w.xlo.view();
+        A.links64 = p.c.links(P64);
+        A.links = p.c.links(prec);
+        A.kappa = p.kappa;
+        A.tol2 = prm.tol * prm.tol;
+        A.delta2 = delta * delta;
+        A.maxiter = prm.maxiter;
+        A.poll = parse_poll(prm);
+        A.st = w.st.as<KState>();
+        A.res2 = w.parts2.as<double>();
+        k_small_bicg(prec, p.c.G->recon, A, w.n, false, user_stream);
+        args.push_back(A);
+    }
+    auto launch = [&](hipStream_t s) {
+        for (size_t k = 0; k < P.size(); ++k) k_small_bicg(prec, P[k].c.G->recon, args[k], P[k].w->n, true, s);
+        DL_HIP(hipGetLastError());
+    };
+    if (prm.use_graph) {
+        CaptureStream cst(user_stream);
+        ChunkGraph cg;
+        cg.begin(cst.s);
+        if (fault_injected("capture")) throw Error{DL_EHIP, "injected fault inside a graph capture"};
+        launch(cst.s);
+        cg.end();
+        DL_HIP(hipGraphLaunch(cg.exec, cst.s));
+        cst.join();
+        // the executable graph lives until its launch has run
+        DL_HIP(hipStreamSynchronize(cst.s));
+    } else {
+        launch(user_stream);
+    }
+    for (const Prob &p : P) p.w->res2_known = true;
+    return true;
+}
+
 // BiCGStab on the even-site Schur systems of every problem (sources in w.be /
 // w.bo, FP64).  Leaves x_e in w.x64, x_o in w.xo and the per right-hand side
 // state in w.st.  Iterated vectors in w.prec; below FP64 the iterate is folded
@@ -1156,6 +1221,7 @@ bool fault_injected(const char *where)
 // of `poll` iterations after the first is replayed from a captured hipGraph.
 void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hipStream_t user_stream)
 {
+    if (small_solve(P0, prm, user_stream)) return;
     std::unique_ptr<CaptureStream> cst;
     if (prm.use_graph) cst.reset(new CaptureStream(user_stream));
     const hipStream_t s = cst ? cst->s : user_stream;
@@ -1282,6 +1348,12 @@ void true_residual_full(const Ctx &c, double kappa, SolveWork &w, std::vector<do
 {
     const int n = w.n;
     double *parts = w.parts.as<double>(), *parts2 = w.parts2.as<double>();
+    if (w.res2_known) {
+        out.resize(n);
+        DL_HIP(hipMemcpyAsync(out.data(), parts2, sizeof(double) * n, hipMemcpyDeviceToHost, c.s));
+        DL_HIP(hipStreamSynchronize(c.s));
+        return;
+    }
     // r_e = b_e - x_e + kappa D_eo x_o ; r_o = b_o - x_o + kappa D_oe x_e
     int nbd = launch_dslash(dcall(c, P64, 0, false, EPI_XMY_NRM, w.xo.view(), w.r64.view(), w.be.view(), w.x64.view(),
                                   kappa, n, parts, nullptr),

@@ -10,7 +10,7 @@
 // at once.
 #include <algorithm>
 
-#include "dl_internal.hpp"
+#include "dl_krylov.hpp"
 
 namespace dl {
 
@@ -79,20 +79,6 @@ __device__ void sum_parts(const double *parts, int rhs, int nblk, double out[NP]
     __syncthreads();  // the next sum may overwrite red
 }
 
-__device__ __forceinline__ void cdiv(const double a[2], const double b[2], double out[2])
-{
-    double d = b[0] * b[0] + b[1] * b[1];
-    double re = (a[0] * b[0] + a[1] * b[1]) / d, im = (a[1] * b[0] - a[0] * b[1]) / d;
-    out[0] = re;
-    out[1] = im;
-}
-__device__ __forceinline__ void cmul(const double a[2], const double b[2], double out[2])
-{
-    double re = a[0] * b[0] - a[1] * b[1], im = a[0] * b[1] + a[1] * b[0];
-    out[0] = re;
-    out[1] = im;
-}
-
 __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
 {
     double b2;
@@ -111,8 +97,7 @@ __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
     a.restart[rhs] = 0;
 }
 
-// (Re)start of the recursion: rho = (rhat, r) from partials [.., 2] (with
-// rhat = r, so |r|^2 is its real part), alpha = omega = 1.
+// partials [.., 2]: (rhat, r)
 __device__ void bicg_rho(const SSeg &a, int rhs)
 {
     if (masked_off(a.mask, rhs)) return;
@@ -120,25 +105,15 @@ __device__ void bicg_rho(const SSeg &a, int rhs)
     sum_parts<2>(a.parts, rhs, a.nblk, rn);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
-    s.rho[0] = rn[0];
-    s.rho[1] = rn[1];
-    s.alpha[0] = s.omega[0] = 1.0;
-    s.alpha[1] = s.omega[1] = 0.0;
-    s.beta[0] = s.beta[1] = 0.0;
-    s.rr = rn[0];
-    s.maxrr = rn[0];
-    if (!isfinite(rn[0]) || !isfinite(rn[1])) {
-        s.nonfinite = 1;
+    bicg_rho_step(s, rn);
+    if (s.nonfinite) {
         a.act[rhs] = 0;
         a.upd[rhs] = 0;
     }
     a.st[rhs] = s;
 }
 
-// After the x / r / p update of an iteration: |r|^2 from partials [.., 1];
-// counts the iteration and flags convergence (or the iteration cap, or a
-// breakdown: rho = 0 or omega = 0) for the FP64 true-residual check, and a
-// reliable update when |r| fell by delta since the last one.
+// partials [.., 1]: |r|^2
 __device__ void bicg_check(const SSeg &a, const SParams &p, int rhs)
 {
     if (!a.act[rhs]) return;
@@ -146,23 +121,10 @@ __device__ void bicg_check(const SSeg &a, const SParams &p, int rhs)
     sum_parts<1>(a.parts, rhs, a.nblk, &rr);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
-    s.iters += 1;
-    s.rr = rr;
-    if (!isfinite(rr) || !isfinite(s.beta[0]) || !isfinite(s.beta[1])) {
-        s.nonfinite = 1;
-        a.act[rhs] = 0;
-        a.upd[rhs] = 0;
-    } else {
-        if (rr <= s.stop2 || s.iters >= s.maxiter || (s.rho[0] == 0 && s.rho[1] == 0) ||
-            (s.omega[0] == 0 && s.omega[1] == 0)) {
-            // converged (or out of iterations, or breakdown): check the FP64 true residual
-            a.act[rhs] = 0;
-            a.upd[rhs] = 1;
-        } else if (p.mixed && rr < s.delta2 * s.maxrr) {
-            a.upd[rhs] = 1;
-        }
-        if (rr > s.maxrr) s.maxrr = rr;
-    }
+    int act = 1, upd = a.upd[rhs];
+    bicg_check_step(s, rr, s.delta2, s.maxiter, p.mixed, act, upd);
+    a.act[rhs] = act;
+    a.upd[rhs] = upd;
     a.st[rhs] = s;
 }
 
@@ -178,52 +140,22 @@ __device__ void bicg_alpha(const SSeg &a, int rhs)
     a.st[rhs] = s;
 }
 
-// omega = (t, s) / |t|^2 from the partials of the hop that made t ([.., 7]:
-// (t, s), |t|^2, (rhat, t), (rhat, s)); the next rho by linearity of
-// r = s - omega t, rho' = (rhat, s) - omega (rhat, t); beta = (rho' / rho)
-// (alpha / omega).  Each dot is taken directly from the vectors of this
-// iteration: nothing accumulates across iterations.  (rhat, s) is zero but for
-// rounding, and it is kept: without it a right-hand side near breakdown lost
-// its way (7.9e-9 after 2000 iterations at a tolerance of 1e-12).  The hop's
-// epilogue reads both of its vectors anyway, so the s update, which summed it
-// before, moves three half fields instead of four.
-// omega = 0 (t = 0, e.g. s = 0 after an exact half step) ends the recursion:
-// beta is set to 0, and the check sends the right-hand side to the FP64 true
-// residual, which either confirms convergence or restarts from it.
+// partials of the hop that made t ([.., 7]): (t, s), |t|^2, (rhat, t), (rhat, s).
+// Its epilogue reads the vectors of the last dot anyway: the s update, which
+// summed it before, moves three half fields instead of four.
 __device__ void bicg_omega(const SSeg &a, int rhs)
 {
     if (!a.act[rhs]) return;
     double d[7];
     sum_parts<7>(a.parts, rhs, a.nblk, d);
-    const double ts[2] = {d[0], d[1]}, tt = d[2], rt[2] = {d[3], d[4]}, rs[2] = {d[5], d[6]};
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
-    if (tt > 0) {
-        s.omega[0] = ts[0] / tt;
-        s.omega[1] = ts[1] / tt;
-    } else {
-        s.omega[0] = s.omega[1] = 0.0;
-    }
-    double wrt[2], rn[2], q[2], ao[2];
-    cmul(s.omega, rt, wrt);
-    rn[0] = rs[0] - wrt[0];
-    rn[1] = rs[1] - wrt[1];
-    if (s.omega[0] == 0 && s.omega[1] == 0) {
-        s.beta[0] = s.beta[1] = 0.0;
-    } else {
-        cdiv(rn, s.rho, q);
-        cdiv(s.alpha, s.omega, ao);
-        cmul(q, ao, s.beta);
-    }
-    s.rho[0] = rn[0];
-    s.rho[1] = rn[1];
+    bicg_omega_step(s, d);
     a.st[rhs] = s;
 }
 
-// After a reliable update replaced r by the FP64 residual: partials [.., 2]
-// (rhat, r) of the replaced r, which rho takes, so that the next alpha matches
-// the r it multiplies (alpha, omega and beta stay); partials2 [.., 1] |r|^2 of
-// the FP64 residual, the true residual of the Schur system.
+// partials [.., 2]: (rhat, r) of the replaced r; partials2 [.., 1]: |r|^2 of the
+// FP64 residual
 __device__ void bicg_update(const SSeg &a, int rhs)
 {
     if (!a.upd[rhs]) {
@@ -235,27 +167,12 @@ __device__ void bicg_update(const SSeg &a, int rhs)
     sum_parts<1>(a.parts2, rhs, a.nblk2, &r2);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
-    s.rho[0] = rn[0];
-    s.rho[1] = rn[1];
-    s.true2 = r2;
-    s.updates += 1;
-    a.restart[rhs] = 0;
-    if (!isfinite(r2)) {
-        s.nonfinite = 1;
-        a.act[rhs] = 0;
-    } else if (r2 <= s.stop2) {
-        s.done = 1;
-        a.act[rhs] = 0;
-    } else if (!a.act[rhs] && s.iters < s.maxiter) {
-        // the iterated residual claimed convergence but the true one disagrees:
-        // restart the recursion from the true residual
-        a.act[rhs] = 1;
-        a.restart[rhs] = 1;
-    }
-    s.maxrr = r2;
-    s.rr = r2;
-    a.st[rhs] = s;
+    int act = a.act[rhs], restart;
+    bicg_update_step(s, rn, r2, s.maxiter, act, restart);
+    a.act[rhs] = act;
+    a.restart[rhs] = restart;
     a.upd[rhs] = 0;
+    a.st[rhs] = s;
 }
 
 __device__ void cg_init(const SSeg &a, const SParams &p, int rhs)

@@ -252,7 +252,7 @@ struct KState {
     int done;       // converged: FP64 true residual below tolerance
     int nonfinite;
     int maxiter;
-    int pad;
+    int due;        // a reliable update is due (small-lattice solver)
 };
 
 int blas_blocks(int64_t Vh);
@@ -310,6 +310,26 @@ enum SOp {
     S_SUM             // out[rhs] = sum of partials
 };
 void scalar_launch(int op, const std::vector<SSeg> &segs, const SParams &p, hipStream_t s);
+
+// ---------------------------------------------------------------- small lattices
+
+// The whole BiCGStab solve of each right-hand side in one workgroup
+// (dl_small.hip), on lattices of up to SMALL_VH sites per parity, in FP64 or
+// FP32 with FP64 reliable updates: sources be, bo to solutions x64, xo, the
+// solver states and the full-lattice squared residuals.  r .. mid and xlo are
+// packed fields of the iteration precision (xlo below FP64 only).
+constexpr int SMALL_VH = 512;
+struct SmallArgs {
+    Geom g;
+    Field be, bo, bhat, x64, xo, mid64, r, rh, p, v, t, mid, xlo;
+    const void *links64, *links;
+    double kappa, tol2, delta2;
+    int maxiter, poll;
+    KState *st;
+    double *res2;
+};
+// launch = false only raises the kernel's LDS limit (once before the launch, outside a capture)
+void k_small_bicg(int prec, int recon, const SmallArgs &A, int nrhs, bool launch, hipStream_t s);
 
 // ---------------------------------------------------------------- fields, sources, traces
 

@@ -125,3 +125,32 @@ def test_smearing_of_the_sources_of_a_loop(dl, dev, dims):
         ref = oracle.loops_accumulate(dims, xi, s, [0, 15])
         scale = np.linalg.norm(xi.reshape(dims[3], -1), axis=1) * np.linalg.norm(s.reshape(dims[3], -1), axis=1)
         assert np.max(np.abs(L[n] - ref) / scale) < 1e-12, n
+
+
+# sites per parity around the edges of the one-kernel solver's variants (128 with two wavefronts to 64 sites, 256 and
+# 512 with one and two sites per thread), and the first size the batched kernels take
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 4), (6, 2, 6, 4), (4, 4, 4, 8), (6, 6, 4, 4), (8, 4, 4, 8),
+                                  (6, 4, 6, 8)])
+def test_solve_of_small_lattices(dl, dev, dims, recon, prec):
+    U = synth.gauge_field(dims, 0.5, seed=951)
+    kappa = 0.12
+    for tap in (1, 0):
+        G = dl.Gauge(dl.Lattice(dims, tap), U, precs=(dl.DL_F64, prec), recon=recon)
+        b = synth.random_spinor(dims, 4, seed=952)
+        b[1] = 0  # solved by x = 0 in no iterations
+        b[2] *= 1e-5
+        b[3, 1:] = 0  # one site
+        x, st = dl.solve(G, kappa, to_dev(b, dev), dl.solve_params(prec=prec, tol=1e-11, maxiter=600))
+        x = from_dev(x)
+        assert st[1] == (dl.DL_OK, 0, 0, 0.0) and not x[1].any()
+        for r in (0, 2, 3):
+            assert st[r][0] == dl.DL_OK and st[r][3] <= 1e-11, st[r]
+            rr = np.linalg.norm(b[r] - oracle.apply_m(U, x[r], dims, kappa, tap)) / np.linalg.norm(b[r])
+            assert rr <= 1.5e-11, (tap, r, rr)
+            assert abs(rr - st[r][3]) <= 1e-13
+        # the cap: the last iterate and its residual come back, and say so
+        x, st = dl.solve(G, kappa, to_dev(b[:1], dev), dl.solve_params(prec=prec, tol=1e-11, maxiter=3))
+        rr = np.linalg.norm(b[0] - oracle.apply_m(U, from_dev(x)[0], dims, kappa, tap)) / np.linalg.norm(b[0])
+        assert st[0][0] == dl.DL_ENOCONV and st[0][1] == 3 and abs(rr - st[0][3]) <= 1e-6 * rr
