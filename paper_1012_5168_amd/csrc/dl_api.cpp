@@ -57,17 +57,24 @@ namespace dl {
 // allocation that takes the block waits on that event, so no kernel still
 // reading or writing the block can race with its next user.  Where no call
 // stream is known the release synchronises the device instead, as hipFree
-// would.  The cached bytes are capped (DL_CACHE_GB, default 64 GB, or
-// dl_cache_set_limit; 0 turns the cache off); dl_cache_release frees all of
-// it; an allocation that fails releases the cache and tries again.
+// would; where the call's stream has run dry by then (most calls end with a
+// synchronisation) no event is needed.  The cached bytes are capped
+// (DL_CACHE_GB, default 64 GB, or dl_cache_set_limit; 0 turns the cache off):
+// the blocks released longest ago make room, so that a process that has moved
+// on to other shapes still has its present ones cached (turned away at a full
+// cache instead, 96 fields at 16^3 x 32 cost 65 ms of mapping memory per
+// dl_apply of 3.5 ms); dl_cache_release frees all of it; an allocation that
+// fails releases the cache and tries again.
 namespace {
 struct CacheEntry {
     void *p;
-    hipEvent_t ready;  // recorded after the block's last use (null: the device was synchronised)
+    hipEvent_t ready;  // recorded after the block's last use (null: its stream was idle)
+    uint64_t stamp;    // order of release
 };
 std::mutex g_cache_mu;
 std::multimap<std::pair<int, size_t>, CacheEntry> g_cache_free;
 size_t g_cache_bytes = 0;
+uint64_t g_cache_stamp = 0;
 bool g_cache_limit_set = false;
 size_t g_cache_limit = 0;
 
@@ -102,11 +109,13 @@ void free_entry(const CacheEntry &c)
     (void)hipFree(c.p);
 }
 
-// free cached blocks until at most `keep` bytes remain
+// free cached blocks, the longest unused first, until at most `keep` bytes remain
 void cache_trim_locked(size_t keep)
 {
     while (g_cache_bytes > keep && !g_cache_free.empty()) {
-        auto it = std::prev(g_cache_free.end());  // largest first
+        auto it = std::min_element(g_cache_free.begin(), g_cache_free.end(), [](const auto &x, const auto &y) {
+            return x.second.stamp < y.second.stamp;
+        });
         free_entry(it->second);
         g_cache_bytes -= it->first.second;
         g_cache_free.erase(it);
@@ -139,7 +148,7 @@ void DevBuf::alloc(size_t n)
     release();
     if (n == 0) return;
     const int dev = current_device();
-    CacheEntry hit{nullptr, nullptr};
+    CacheEntry hit{nullptr, nullptr, 0};
     {
         std::lock_guard<std::mutex> lk(g_cache_mu);
         auto it = g_cache_free.lower_bound({dev, n});
@@ -190,13 +199,14 @@ void DevBuf::release() noexcept
     {
         std::lock_guard<std::mutex> lk(g_cache_mu);
         limit = cache_limit_locked();
-        if (g_cache_bytes + cap > limit) limit = 0;
     }
-    if (limit > 0) {
-        CacheEntry c{p, nullptr};
+    if (cap <= limit) {
+        CacheEntry c{p, nullptr, 0};
         bool idle = false;
         if (t_stream_known && !capturing(t_stream)) {
-            if (hipEventCreateWithFlags(&c.ready, hipEventDisableTiming) == hipSuccess) {
+            if (hipStreamQuery(t_stream) == hipSuccess) {
+                idle = true;
+            } else if (hipEventCreateWithFlags(&c.ready, hipEventDisableTiming) == hipSuccess) {
                 if (hipEventRecord(c.ready, t_stream) == hipSuccess) {
                     idle = true;
                 } else {
@@ -211,7 +221,10 @@ void DevBuf::release() noexcept
         if (idle) {
             try {
                 std::lock_guard<std::mutex> lk(g_cache_mu);
-                if (g_cache_bytes + cap <= cache_limit_locked()) {
+                const size_t now = cache_limit_locked();
+                if (cap <= now) {
+                    cache_trim_locked(now - cap);
+                    c.stamp = ++g_cache_stamp;
                     g_cache_free.insert({{current_device(), cap}, c});
                     g_cache_bytes += cap;
                     cached = true;
@@ -227,6 +240,68 @@ void DevBuf::release() noexcept
     p = nullptr;
     bytes = 0;
     cap = 0;
+}
+
+// Page-locked host blocks, kept for later calls up to PIN_KEEP bytes in all
+// (allocating one costs more than the small copies it serves).
+namespace {
+constexpr size_t PIN_KEEP = 32u << 20;
+std::mutex g_pin_mu;
+std::multimap<size_t, void *> g_pin_free;
+size_t g_pin_bytes = 0;
+
+void pin_release_all()
+{
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    for (auto &e : g_pin_free) (void)hipHostFree(e.second);
+    g_pin_free.clear();
+    g_pin_bytes = 0;
+}
+}  // namespace
+
+PinBuf::PinBuf(size_t n, hipStream_t s) : bytes(n), stream(s)
+{
+    if (n == 0) return;
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        auto it = g_pin_free.lower_bound(n);
+        if (it != g_pin_free.end() && it->first <= std::max<size_t>(4 * n, 65536)) {
+            cap = it->first;
+            p = it->second;
+            g_pin_bytes -= cap;
+            g_pin_free.erase(it);
+            return;
+        }
+    }
+    cap = std::max<size_t>(n, 16384);
+    const hipError_t e = hipHostMalloc(&p, cap, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+        throw Error{DL_ENOMEM, "hipHostMalloc of " + std::to_string(cap) + " bytes failed: " + hipGetErrorString(e)};
+    }
+}
+
+void PinBuf::fetch(const void *src, size_t n, size_t at)
+{
+    busy = true;
+    DL_HIP(hipMemcpyAsync(static_cast<char *>(p) + at, src, n, hipMemcpyDeviceToHost, stream));
+}
+
+PinBuf::~PinBuf()
+{
+    if (!p) return;
+    if (busy) (void)hipStreamSynchronize(stream);  // an error left a copy under way
+    try {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        if (g_pin_bytes + cap <= PIN_KEEP) {
+            g_pin_free.insert({cap, p});
+            g_pin_bytes += cap;
+            return;
+        }
+    } catch (...) {
+    }
+    (void)hipHostFree(p);
 }
 
 void HalfField::alloc(int prec_, int64_t nrhs_, int64_t Vh_)
@@ -582,7 +657,7 @@ extern "C" void dl_gauge_destroy(dl_gauge g) { delete g; }
 // ====================================================================== gamma matrices
 
 // Gamma_n = g1^n0 g2^n1 g3^n2 g4^n3 in the chiral basis, as [16][4][4][re,im]
-static std::vector<double> gamma_table()
+static std::vector<double> make_gamma_table()
 {
     using C = std::complex<double>;
     const C I(0, 1);
@@ -614,6 +689,29 @@ static std::vector<double> gamma_table()
             }
     }
     return out;
+}
+
+static const std::vector<double> &gamma_table()
+{
+    static const std::vector<double> t = make_gamma_table();
+    return t;
+}
+
+// The chosen Gammas as what they are, one entry of +-1 or +-i per row.
+static GammaSet gamma_set(const std::vector<double> &gtab, const int32_t *gammas, int n_gamma)
+{
+    GammaSet s = {};
+    s.n = n_gamma;
+    for (int k = 0; k < n_gamma; ++k)
+        for (int r = 0; r < 4; ++r)
+            for (int c = 0; c < 4; ++c) {
+                const double *z = gtab.data() + gammas[k] * 32 + 2 * (4 * r + c);
+                if (z[0] == 0 && z[1] == 0) continue;
+                s.col[k][r] = (int8_t)c;
+                s.re[k][r] = (int8_t)z[0];
+                s.im[k][r] = (int8_t)z[1];
+            }
+    return s;
 }
 
 // ====================================================================== operators
@@ -1050,18 +1148,24 @@ struct FlagCount {
 FlagCount count_flags(const std::vector<Prob> &P, hipStream_t s)
 {
     FlagCount c;
-    std::vector<std::vector<int>> h(P.size());
-    for (size_t k = 0; k < P.size(); ++k) {
-        h[k].resize(3 * (size_t)P[k].w->n);
-        DL_HIP(hipMemcpyAsync(h[k].data(), P[k].w->flags.p, sizeof(int) * h[k].size(), hipMemcpyDeviceToHost, s));
+    size_t total = 0;
+    for (const Prob &p : P) total += 3 * (size_t)p.w->n;
+    PinBuf pin(sizeof(int) * total, s);
+    size_t at = 0;
+    for (const Prob &p : P) {
+        pin.fetch(p.w->flags.p, sizeof(int) * 3 * p.w->n, at);
+        at += sizeof(int) * 3 * p.w->n;
     }
-    DL_HIP(hipStreamSynchronize(s));
-    for (size_t k = 0; k < P.size(); ++k)
-        for (int i = 0, n = P[k].w->n; i < n; ++i) {
-            c.act += h[k][i] != 0;
-            c.upd += h[k][n + i] != 0;
-            c.restart += h[k][2 * n + i] != 0;
+    pin.wait();
+    const int *h = pin.as<int>();
+    for (const Prob &p : P) {
+        for (int i = 0, n = p.w->n; i < n; ++i) {
+            c.act += h[i] != 0;
+            c.upd += h[n + i] != 0;
+            c.restart += h[2 * n + i] != 0;
         }
+        h += 3 * p.w->n;
+    }
     return c;
 }
 
@@ -1343,17 +1447,12 @@ void bicgstab_batch(const Ctx &c, double kappa, const dl_solve_params &prm, Solv
     bicgstab_multi({Prob{c, kappa, &w}}, prm, c.s);
 }
 
-// Full-lattice FP64 true residual |b - M x|^2 per right-hand side into out[n].
-void true_residual_full(const Ctx &c, double kappa, SolveWork &w, std::vector<double> &out)
+// Full-lattice FP64 true residual |b - M x|^2 per right-hand side, the even and
+// the odd sites' sums one after the other in `sums` (2 n doubles, device).
+void true_residual_full(const Ctx &c, double kappa, SolveWork &w, DevBuf &sums)
 {
     const int n = w.n;
     double *parts = w.parts.as<double>(), *parts2 = w.parts2.as<double>();
-    if (w.res2_known) {
-        out.resize(n);
-        DL_HIP(hipMemcpyAsync(out.data(), parts2, sizeof(double) * n, hipMemcpyDeviceToHost, c.s));
-        DL_HIP(hipStreamSynchronize(c.s));
-        return;
-    }
     // r_e = b_e - x_e + kappa D_eo x_o ; r_o = b_o - x_o + kappa D_oe x_e
     int nbd = launch_dslash(dcall(c, P64, 0, false, EPI_XMY_NRM, w.xo.view(), w.r64.view(), w.be.view(), w.x64.view(),
                                   kappa, n, parts, nullptr),
@@ -1361,7 +1460,7 @@ void true_residual_full(const Ctx &c, double kappa, SolveWork &w, std::vector<do
     launch_dslash(dcall(c, P64, 1, false, EPI_XMY_NRM, w.x64.view(), w.tmp64.view(), w.bo.view(), w.xo.view(), kappa,
                         n, parts2, nullptr),
                   c.s);
-    DevBuf sums(sizeof(double) * 2 * n);
+    sums.alloc(sizeof(double) * 2 * n);
     SSeg a;
     a.parts = parts;
     a.nblk = nbd;
@@ -1371,11 +1470,6 @@ void true_residual_full(const Ctx &c, double kappa, SolveWork &w, std::vector<do
     a.parts = parts2;
     a.out = sums.as<double>() + n;
     scalar_launch(S_SUM, {a}, SParams{}, c.s);
-    std::vector<double> h(2 * n);
-    DL_HIP(hipMemcpyAsync(h.data(), sums.p, sizeof(double) * 2 * n, hipMemcpyDeviceToHost, c.s));
-    DL_HIP(hipStreamSynchronize(c.s));
-    out.resize(n);
-    for (int i = 0; i < n; ++i) out[i] = h[i] + h[n + i];
 }
 
 // Truncated CGNR (x0 = 0, exactly `iters` iterations) on the normal equations
@@ -1510,33 +1604,54 @@ double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
     return k.iters * 23.0 * fb + k.updates * upd + 10.0 * f8 + 4.0 * fb;
 }
 
-// Per right-hand side statistics of the solve just finished; `seconds` is the
-// solve's share of the wall time since the stopwatch's last lap (the batch's
-// time divided by its right-hand sides).
-void fill_stats(const SolveWork &w, const std::vector<double> &res2, dl_solve_stats *out, hipStream_t s,
-                bool cgnr, Stopwatch &sw, double secs_per_rhs = -1.0)
-{
-    std::vector<KState> h(w.n);
-    DL_HIP(hipMemcpyAsync(h.data(), w.st.p, sizeof(KState) * w.n, hipMemcpyDeviceToHost, s));
-    DL_HIP(hipStreamSynchronize(s));
-    const double secs = secs_per_rhs >= 0 ? secs_per_rhs : sw.lap() / std::max(1, w.n);
-    for (int i = 0; i < w.n; ++i) {
-        dl_solve_stats &o = out[i];
-        o.iters = h[i].iters;
-        o.reliable_updates = h[i].updates;
-        o.pad = 0;
-        const double b2 = h[i].b2;
-        o.true_rel_residual = (i < (int)res2.size() && b2 > 0) ? std::sqrt(res2[i] / b2) : 0.0;
-        if (h[i].nonfinite)
-            o.status = DL_ENAN;
-        else if (cgnr || h[i].done)
-            o.status = DL_OK;
-        else
-            o.status = DL_ENOCONV;
-        o.seconds = secs;
-        o.bytes = solve_bytes(w, h[i], cgnr);
+// The statistics of a solve: the solver states and, where asked for, the true
+// residuals are computed and copied behind the solve (the constructor), without
+// waiting, so that whatever follows the solve is not held up; fill() waits and
+// writes them out.  `seconds` is the solve's share of the wall time since the
+// stopwatch's last lap (the batch's time divided by its right-hand sides).
+struct SolveReport {
+    int n;
+    bool cgnr, residual, split;  // split: the residual comes as two sums per right-hand side
+    const SolveWork *w;
+    DevBuf sums;
+    PinBuf pin;
+    SolveReport(const Ctx &c, double kappa, SolveWork &w_, bool cgnr_, bool residual_)
+        : n(w_.n), cgnr(cgnr_), residual(residual_), split(!w_.res2_known), w(&w_),
+          pin((sizeof(KState) + 2 * sizeof(double)) * w_.n, c.s)
+    {
+        const double *res = w_.parts2.as<double>();
+        if (residual && split) {
+            true_residual_full(c, kappa, w_, sums);
+            res = sums.as<double>();
+        }
+        pin.fetch(w_.st.p, sizeof(KState) * n, 0);
+        if (residual) pin.fetch(res, sizeof(double) * n * (split ? 2 : 1), sizeof(KState) * n);
     }
-}
+    void fill(dl_solve_stats *out, Stopwatch &sw, double secs_per_rhs = -1.0)
+    {
+        pin.wait();
+        const KState *h = pin.as<KState>();
+        const double *res = reinterpret_cast<const double *>(h + n);
+        const double secs = secs_per_rhs >= 0 ? secs_per_rhs : sw.lap() / std::max(1, n);
+        for (int i = 0; i < n; ++i) {
+            dl_solve_stats &o = out[i];
+            o.iters = h[i].iters;
+            o.reliable_updates = h[i].updates;
+            o.pad = 0;
+            const double b2 = h[i].b2;
+            o.true_rel_residual =
+                (residual && b2 > 0) ? std::sqrt((res[i] + (split ? res[n + i] : 0.0)) / b2) : 0.0;
+            if (h[i].nonfinite)
+                o.status = DL_ENAN;
+            else if (cgnr || h[i].done)
+                o.status = DL_OK;
+            else
+                o.status = DL_ENOCONV;
+            o.seconds = secs;
+            o.bytes = solve_bytes(*w, h[i], cgnr);
+        }
+    }
+};
 
 }  // namespace
 
@@ -1564,7 +1679,6 @@ extern "C" int dl_solve(dl_gauge G, double kappa, const dl_solve_params *params,
             SolveWork w;
             const double *bsrc = static_cast<const double *>(b) + r0 * V * 24;
             double *xdst = static_cast<double *>(x) + r0 * V * 24;
-            std::vector<double> res2;
             if (cg) {
                 w.alloc_cgnr(prm.prec, n, Vh);
                 k_pack(prm.prec, w.be.view(), w.bo.view(), bsrc, c.g, n, c.s);
@@ -1574,13 +1688,12 @@ extern "C" int dl_solve(dl_gauge G, double kappa, const dl_solve_params *params,
                 w.alloc_bicg(prm.prec, n, Vh);
                 k_pack(P64, w.be.view(), w.bo.view(), bsrc, c.g, n, c.s);
                 bicgstab_batch(c, kappa, prm, w);
-                true_residual_full(c, kappa, w, res2);
                 k_unpack(P64, w.x64.view(), w.xo.view(), xdst, c.g, n, c.s);
             }
+            SolveReport report(c, kappa, w, cg, !cg);
             DL_HIP(hipGetLastError());
-            DL_HIP(hipStreamSynchronize(c.s));
             std::vector<dl_solve_stats> st(n);
-            fill_stats(w, res2, st.data(), c.s, cg, sw);
+            report.fill(st.data(), sw);
             for (int i = 0; i < n; ++i) {
                 if (stats) stats[r0 + i] = st[i];
                 if (st[i].status != DL_OK && worst == DL_OK) worst = st[i].status;
@@ -1623,6 +1736,22 @@ void validate_sources(const dl_lattice_s &lat, const dl_sources *src)
 
 int source_classes(const dl_sources *src) { return src->kind == DL_SRC_POINT ? 12 : dilution_classes(src->scheme); }
 
+// the right-hand sides of a description from number `first` on
+SourceSpec source_spec(const dl_sources &src, const dl_lattice_s &lat, int64_t first)
+{
+    SourceSpec ss;
+    ss.kind = src.kind;
+    ss.scheme = src.kind == DL_SRC_POINT ? 0 : src.scheme;
+    ss.seed = src.seed;
+    ss.V = lat.V;
+    ss.T = lat.dims[3];
+    ss.point_site = src.point_site;
+    ss.first_noise = src.first_noise;
+    ss.first_rhs = first;
+    ss.ncls = source_classes(&src);
+    return ss;
+}
+
 }  // namespace
 
 extern "C" int64_t dl_sources_count(dl_lattice lat, const dl_sources *src)
@@ -1651,29 +1780,11 @@ extern "C" int dl_sources_fill(dl_lattice lat, const dl_sources *src, int64_t fi
         hipStream_t s = static_cast<hipStream_t>(stream);
         const Geom g = lat->geom();
         const int n = (int)nrhs;
-        std::vector<int64_t> hnoise(n);
-        std::vector<int> hcls(n);
-        for (int i = 0; i < n; ++i) {
-            hnoise[i] = src->first_noise + (first_rhs + i) / ncls;
-            hcls[i] = (int)((first_rhs + i) % ncls);
-        }
-        DevBuf dnoise(sizeof(int64_t) * n), dcls(sizeof(int) * n);
-        DL_HIP(hipMemcpyAsync(dnoise.p, hnoise.data(), dnoise.bytes, hipMemcpyHostToDevice, s));
-        DL_HIP(hipMemcpyAsync(dcls.p, hcls.data(), dcls.bytes, hipMemcpyHostToDevice, s));
-        SourceSpec ss;
-        ss.kind = src->kind;
-        ss.scheme = src->kind == DL_SRC_POINT ? 0 : src->scheme;
-        ss.seed = src->seed;
-        ss.V = lat->V;
-        ss.T = lat->dims[3];
-        ss.point_site = src->point_site;
-        ss.noise = dnoise.as<int64_t>();
-        ss.cls = dcls.as<int>();
+        const SourceSpec ss = source_spec(*src, *lat, first_rhs);
         HalfField fe, fo;
         fe.alloc(P64, n, lat->Vh);
         fo.alloc(P64, n, lat->Vh);
-        k_source(P64, fe.view(), 0, ss, g, n, s);
-        k_source(P64, fo.view(), 1, ss, g, n, s);
+        k_source(P64, fe.view(), fo.view(), ss, g, n, s);
         k_unpack(P64, fe.view(), fo.view(), static_cast<double *>(out), g, n, s);
         DL_HIP(hipGetLastError());
         DL_HIP(hipStreamSynchronize(s));
@@ -1743,12 +1854,11 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
     const int64_t total = (int64_t)src->n_noise * ncls;
     const int nsolve = mode == MODE_LOOPS ? 1 : (mode == MODE_GRAD && dout_host) ? 3 : 2;
     const int B = batch_size(per, total, ncls);
-    std::vector<double> gtab = gamma_table();
-    DevBuf dgam(gtab.size() * sizeof(double)), dgidx(sizeof(int) * n_gamma), dA, dgrad;
+    const std::vector<double> &gtab = gamma_table();
+    const GammaSet gset = gamma_set(gtab, gammas, n_gamma);
+    DevBuf dA, dgrad;
     DevBuf dloops((size_t)src->n_noise * n_gamma * T * 2 * sizeof(double)), ddk;
     if (dout_host) ddk.alloc(dloops.bytes);
-    DL_HIP(hipMemcpyAsync(dgam.p, gtab.data(), dgam.bytes, hipMemcpyHostToDevice, c.s));
-    DL_HIP(hipMemcpyAsync(dgidx.p, gammas, dgidx.bytes, hipMemcpyHostToDevice, c.s));
     if (mode == MODE_GRAD) {
         std::vector<double> A = adjoint_matrices(gtab, gammas, n_gamma, W, T, src->n_noise);
         dA.alloc(A.size() * sizeof(double));
@@ -1756,39 +1866,23 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
         dgrad.alloc((size_t)4 * V * 9 * 16);
         zero_launch(dgrad.p, (int64_t)4 * V * 9, c.s);  // [4][V][9] complex
     }
+    // small results come back through page-locked memory; large ones are not worth locking it for
+    const bool pinned = dloops.bytes + ddk.bytes <= (4u << 20);
+    PinBuf loops_pin(pinned ? dloops.bytes + ddk.bytes : 0, c.s);
     int worst = DL_OK;
     Stopwatch sw;
-    std::vector<int64_t> hnoise;
-    std::vector<int> hcls;
     for (int64_t r0 = 0; r0 < total; r0 += B) {
         const int n = (int)std::min<int64_t>(B, total - r0);
         const int nn = n / ncls;
-        hnoise.resize(n);
-        hcls.resize(n);
-        for (int i = 0; i < n; ++i) {
-            hnoise[i] = src->first_noise + (r0 + i) / ncls;
-            hcls[i] = (int)((r0 + i) % ncls);
-        }
-        DevBuf dnoise(sizeof(int64_t) * n), dcls(sizeof(int) * n), dC((size_t)n * T * 32 * sizeof(double));
-        DL_HIP(hipMemcpyAsync(dnoise.p, hnoise.data(), dnoise.bytes, hipMemcpyHostToDevice, c.s));
-        DL_HIP(hipMemcpyAsync(dcls.p, hcls.data(), dcls.bytes, hipMemcpyHostToDevice, c.s));
-        SourceSpec ss;
-        ss.kind = src->kind;
-        ss.scheme = src->kind == DL_SRC_POINT ? 0 : src->scheme;
-        ss.seed = src->seed;
-        ss.V = V;
-        ss.T = T;
-        ss.point_site = src->point_site;
-        ss.noise = dnoise.as<int64_t>();
-        ss.cls = dcls.as<int>();
+        DevBuf dC((size_t)n * T * 32 * sizeof(double));
+        const SourceSpec ss = source_spec(*src, G->lat, r0);
         // smeared sources: xi = F^iters eta in FP64, kept for the trace
         HalfField xe, xo, te, to;
         SourceSpec sx = ss;
         if (smear_iters > 0) {
             xe.alloc(P64, n, Vh);
             xo.alloc(P64, n, Vh);
-            k_source(P64, xe.view(), 0, ss, c.g, n, c.s);
-            k_source(P64, xo.view(), 1, ss, c.g, n, c.s);
+            k_source(P64, xe.view(), xo.view(), ss, c.g, n, c.s);
             HalfField *ae = &xe, *ao = &xo, *be = &te, *bo = &to;
             if (smear_chip_fits(c.g, n)) {
                 k_smear_chip(c.links(P64), G->recon, SmearIO{{xe.data.p, xo.data.p}, {xe.data.p, xo.data.p}}, false,
@@ -1812,26 +1906,23 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                 k_copy(prec, be, P64, sx.xe, Vh, n, nullptr, c.s);
                 k_copy(prec, bo, P64, sx.xo, Vh, n, nullptr, c.s);
             } else {
-                k_source(prec, be, 0, ss, c.g, n, c.s);
-                k_source(prec, bo, 1, ss, c.g, n, c.s);
+                k_source(prec, be, bo, ss, c.g, n, c.s);
             }
         };
         SolveWork w;
-        std::vector<std::vector<dl_solve_stats>> st(nsolve, std::vector<dl_solve_stats>(n));
+        std::vector<std::unique_ptr<SolveReport>> report(nsolve);
         int sol_prec = P64;
         if (cg) {
             w.alloc_cgnr(prm.prec, n, Vh);
             make_source(prm.prec, w.be.view(), w.bo.view());
             cgnr_batch(c, kappa, prm.fixed_iters, w);
             sol_prec = prm.prec;
-            fill_stats(w, {}, st[0].data(), c.s, true, sw);
+            report[0].reset(new SolveReport(c, kappa, w, true, false));
         } else {
-            std::vector<double> res2;
             w.alloc_bicg(prm.prec, n, Vh);
             make_source(P64, w.be.view(), w.bo.view());
             bicgstab_batch(c, kappa, prm, w);
-            if (stats) true_residual_full(c, kappa, w, res2);
-            fill_stats(w, res2, st[0].data(), c.s, false, sw);
+            report[0].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
             if (mode == MODE_DKAPPA) {
                 // second solve on w = D s (sources are regenerated for the trace)
                 launch_dslash(dcall(c, P64, 0, false, EPI_PLAIN, w.xo.view(), w.be.view(), NOF, NOF, 1.0, n, nullptr,
@@ -1841,9 +1932,7 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                                     nullptr, nullptr),
                               c.s);
                 bicgstab_batch(c, kappa, prm, w);
-                res2.clear();
-                if (stats) true_residual_full(c, kappa, w, res2);
-                fill_stats(w, res2, st[1].data(), c.s, false, sw);
+                report[1].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
             } else if (mode == MODE_GRAD) {
                 HalfField se, so;
                 se.alloc(P64, n, Vh);
@@ -1852,7 +1941,7 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                 k_copy(P64, so.view(), P64, w.xo.view(), Vh, n, nullptr, c.s);
                 if (out_host) {
                     k_trace(P64, se.view(), so.view(), ss, c.g, n, dC.as<double>(), c.s);
-                    k_gamma_contract(dC.as<double>(), nn, ncls, T, dgam.as<double>(), dgidx.as<int>(), n_gamma,
+                    k_gamma_contract(dC.as<double>(), nn, ncls, T, gset,
                                      dloops.as<double>() + (r0 / ncls) * n_gamma * T * 2, c.s);
                 }
                 if (dout_host) {
@@ -1864,42 +1953,50 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                                         nullptr, nullptr),
                                   c.s);
                     bicgstab_batch(c, kappa, prm, w);
-                    res2.clear();
-                    if (stats) true_residual_full(c, kappa, w, res2);
-                    fill_stats(w, res2, st[2].data(), c.s, false, sw);
+                    report[2].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
                     k_trace(P64, w.x64.view(), w.xo.view(), ss, c.g, n, dC.as<double>(), c.s);
-                    k_gamma_contract(dC.as<double>(), nn, ncls, T, dgam.as<double>(), dgidx.as<int>(), n_gamma,
+                    k_gamma_contract(dC.as<double>(), nn, ncls, T, gset,
                                      ddk.as<double>() + (r0 / ncls) * n_gamma * T * 2, c.s);
                 }
                 const double *Ab = dA.as<double>();
-                k_adjoint_source(w.be.view(), 0, ss, c.g, n, Ab, src->first_noise, c.s);
-                k_adjoint_source(w.bo.view(), 1, ss, c.g, n, Ab, src->first_noise, c.s);
+                k_adjoint_source(w.be.view(), w.bo.view(), ss, c.g, n, Ab, c.s);
                 bicgstab_batch(c, kappa, prm, w);
-                res2.clear();
-                if (stats) true_residual_full(c, kappa, w, res2);
-                fill_stats(w, res2, st[1].data(), c.s, false, sw);
+                report[1].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
                 k_link_grad(se.view(), so.view(), w.x64.view(), w.xo.view(), c.g, n, kappa, dgrad.as<double>(),
                             c.s);
-                DL_HIP(hipStreamSynchronize(c.s));
             }
         }
         if (mode != MODE_GRAD) {
             k_trace(sol_prec, w.x64.view(), w.xo.view(), sx, c.g, n, dC.as<double>(), c.s);
-            k_gamma_contract(dC.as<double>(), nn, ncls, T, dgam.as<double>(), dgidx.as<int>(), n_gamma,
+            k_gamma_contract(dC.as<double>(), nn, ncls, T, gset,
                              dloops.as<double>() + (r0 / ncls) * n_gamma * T * 2, c.s);
         }
         DL_HIP(hipGetLastError());
+        const bool last = r0 + B >= total;
+        if (last) {
+            if (out_host && pinned) loops_pin.fetch(dloops.p, dloops.bytes, 0);
+            if (out_host && !pinned)
+                DL_HIP(hipMemcpyAsync(out_host, dloops.p, dloops.bytes, hipMemcpyDeviceToHost, c.s));
+            if (dout_host && pinned) loops_pin.fetch(ddk.p, ddk.bytes, dloops.bytes);
+            if (dout_host && !pinned)
+                DL_HIP(hipMemcpyAsync(dout_host, ddk.p, ddk.bytes, hipMemcpyDeviceToHost, c.s));
+            if (grad_host) DL_HIP(hipMemcpyAsync(grad_host, dgrad.p, dgrad.bytes, hipMemcpyDefault, c.s));
+        }
         DL_HIP(hipStreamSynchronize(c.s));
-        for (int k = 0; k < nsolve; ++k)
+        // each solve's share of the round's time: the solves of one round are alike
+        const double secs = sw.lap() / ((double)nsolve * n);
+        std::vector<dl_solve_stats> st(n);
+        for (int k = 0; k < nsolve; ++k) {
+            report[k]->fill(st.data(), sw, secs);
             for (int i = 0; i < n; ++i) {
-                if (stats) stats[(int64_t)k * total + r0 + i] = st[k][i];
-                if (st[k][i].status != DL_OK && worst == DL_OK) worst = st[k][i].status;
+                if (stats) stats[(int64_t)k * total + r0 + i] = st[i];
+                if (st[i].status != DL_OK && worst == DL_OK) worst = st[i].status;
             }
+        }
     }
-    if (out_host) DL_HIP(hipMemcpyAsync(out_host, dloops.p, dloops.bytes, hipMemcpyDeviceToHost, c.s));
-    if (grad_host) DL_HIP(hipMemcpyAsync(grad_host, dgrad.p, dgrad.bytes, hipMemcpyDefault, c.s));
-    if (dout_host) DL_HIP(hipMemcpyAsync(dout_host, ddk.p, ddk.bytes, hipMemcpyDeviceToHost, c.s));
-    DL_HIP(hipStreamSynchronize(c.s));
+    loops_pin.wait();
+    if (out_host && pinned) std::memcpy(out_host, loops_pin.as<char>(), dloops.bytes);
+    if (dout_host && pinned) std::memcpy(dout_host, loops_pin.as<char>() + dloops.bytes, ddk.bytes);
     if (worst != DL_OK) g_err = "at least one solve did not converge";
     return worst;
 }
@@ -2161,10 +2258,7 @@ extern "C" int dl_batch_loops(int32_t n_lat, const dl_gauge *gauges, const doubl
         }
         const int kmax = (int)std::max<int64_t>(1, std::min<int64_t>(max_noise, workspace_limit() / per_noise_all));
         const int k = (max_noise + (max_noise + kmax - 1) / kmax - 1) / ((max_noise + kmax - 1) / kmax);  // equal rounds
-        std::vector<double> gtab = gamma_table();
-        DevBuf dgam(gtab.size() * sizeof(double)), dgidx(sizeof(int) * n_gamma);
-        DL_HIP(hipMemcpyAsync(dgam.p, gtab.data(), dgam.bytes, hipMemcpyHostToDevice, s));
-        DL_HIP(hipMemcpyAsync(dgidx.p, gammas, dgidx.bytes, hipMemcpyHostToDevice, s));
+        const GammaSet gset = gamma_set(gamma_table(), gammas, n_gamma);
         std::vector<DevBuf> dloops(n_lat);
         for (int l = 0; l < n_lat; ++l)
             dloops[l].alloc((size_t)srcs[l].n_noise * n_gamma * gauges[l]->lat.dims[3] * 2 * sizeof(double));
@@ -2172,7 +2266,7 @@ extern "C" int dl_batch_loops(int32_t n_lat, const dl_gauge *gauges, const doubl
         Stopwatch sw;
         for (int n0 = 0; n0 < max_noise; n0 += k) {
             std::vector<std::unique_ptr<SolveWork>> work;
-            std::vector<DevBuf> dnoise, dcls, dC;
+            std::vector<DevBuf> dC;
             std::vector<SourceSpec> spec;
             std::vector<Prob> P;
             std::vector<int> lat_of, r0_of, n_of;
@@ -2182,61 +2276,45 @@ extern "C" int dl_batch_loops(int32_t n_lat, const dl_gauge *gauges, const doubl
                 const int ncls = source_classes(&srcs[l]);
                 const int n = nn * ncls;
                 dl_gauge G = gauges[l];
-                std::vector<int64_t> hn(n);
-                std::vector<int> hc(n);
-                for (int i = 0; i < n; ++i) {
-                    hn[i] = srcs[l].first_noise + n0 + i / ncls;
-                    hc[i] = i % ncls;
-                }
-                dnoise.emplace_back(sizeof(int64_t) * n);
-                dcls.emplace_back(sizeof(int) * n);
                 dC.emplace_back((size_t)n * G->lat.dims[3] * 32 * sizeof(double));
-                DL_HIP(hipMemcpyAsync(dnoise.back().p, hn.data(), dnoise.back().bytes, hipMemcpyHostToDevice, s));
-                DL_HIP(hipMemcpyAsync(dcls.back().p, hc.data(), dcls.back().bytes, hipMemcpyHostToDevice, s));
-                SourceSpec ss;
-                ss.kind = srcs[l].kind;
-                ss.scheme = srcs[l].kind == DL_SRC_POINT ? 0 : srcs[l].scheme;
-                ss.seed = srcs[l].seed;
-                ss.V = G->lat.V;
-                ss.T = G->lat.dims[3];
-                ss.point_site = srcs[l].point_site;
-                ss.noise = dnoise.back().as<int64_t>();
-                ss.cls = dcls.back().as<int>();
+                const SourceSpec ss = source_spec(srcs[l], G->lat, (int64_t)n0 * ncls);
                 spec.push_back(ss);
                 work.emplace_back(new SolveWork);
                 SolveWork &w = *work.back();
                 w.alloc_bicg(prm.prec, n, G->lat.Vh);
                 Ctx c{G, G->lat.geom(), s};
-                k_source(P64, w.be.view(), 0, ss, c.g, n, s);
-                k_source(P64, w.bo.view(), 1, ss, c.g, n, s);
+                k_source(P64, w.be.view(), w.bo.view(), ss, c.g, n, s);
                 P.push_back(Prob{c, kappas[l], &w});
                 lat_of.push_back(l);
                 n_of.push_back(nn);
             }
             bicgstab_multi(P, prm, s);
-            DL_HIP(hipStreamSynchronize(s));
+            std::vector<std::unique_ptr<SolveReport>> report;
             int round_rhs = 0;
-            for (const Prob &p : P) round_rhs += p.w->n;
-            const double secs_per_rhs = sw.lap() / std::max(1, round_rhs);
             for (size_t q = 0; q < P.size(); ++q) {
                 const int l = lat_of[q];
                 SolveWork &w = *P[q].w;
                 const int ncls = source_classes(&srcs[l]);
                 const int T = P[q].c.g.T;
-                std::vector<double> res2;
-                if (stats && stats[l]) true_residual_full(P[q].c, kappas[l], w, res2);
+                round_rhs += w.n;
+                report.emplace_back(new SolveReport(P[q].c, kappas[l], w, false, stats && stats[l]));
                 k_trace(P64, w.x64.view(), w.xo.view(), spec[q], P[q].c.g, w.n, dC[q].as<double>(), s);
-                k_gamma_contract(dC[q].as<double>(), n_of[q], ncls, T, dgam.as<double>(), dgidx.as<int>(), n_gamma,
+                k_gamma_contract(dC[q].as<double>(), n_of[q], ncls, T, gset,
                                  dloops[l].as<double>() + (size_t)n0 * n_gamma * T * 2, s);
-                std::vector<dl_solve_stats> st(w.n);
-                fill_stats(w, res2, st.data(), s, false, sw, secs_per_rhs);
-                for (int i = 0; i < w.n; ++i) {
+            }
+            DL_HIP(hipGetLastError());
+            DL_HIP(hipStreamSynchronize(s));
+            const double secs_per_rhs = sw.lap() / std::max(1, round_rhs);
+            for (size_t q = 0; q < P.size(); ++q) {
+                const int l = lat_of[q];
+                const int ncls = source_classes(&srcs[l]);
+                std::vector<dl_solve_stats> st(P[q].w->n);
+                report[q]->fill(st.data(), sw, secs_per_rhs);
+                for (size_t i = 0; i < st.size(); ++i) {
                     if (stats && stats[l]) stats[l][(int64_t)n0 * ncls + i] = st[i];
                     if (st[i].status != DL_OK && worst == DL_OK) worst = st[i].status;
                 }
             }
-            DL_HIP(hipGetLastError());
-            DL_HIP(hipStreamSynchronize(s));
         }
         for (int l = 0; l < n_lat; ++l)
             DL_HIP(hipMemcpyAsync(loops[l], dloops[l].p, dloops[l].bytes, hipMemcpyDeviceToHost, s));
@@ -2288,8 +2366,11 @@ extern "C" int dl_eta_prime_fit(const double *d, const double *c_pi, int32_t ncf
 extern "C" int dl_cache_release(void)
 {
     return guarded([&]() {
-        std::lock_guard<std::mutex> lk(g_cache_mu);
-        cache_trim_locked(0);
+        {
+            std::lock_guard<std::mutex> lk(g_cache_mu);
+            cache_trim_locked(0);
+        }
+        pin_release_all();
         return DL_OK;
     });
 }

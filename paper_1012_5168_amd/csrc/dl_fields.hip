@@ -46,19 +46,20 @@ __device__ __forceinline__ int dil_class(int scheme, const Site &s, int spin, in
 __device__ __forceinline__ void source_site(const SourceSpec &src, int rhs, const Site &st, int64_t lex,
                                             cx<double> eta[12])
 {
-    const int cls = src.cls[rhs];
+    const int64_t number = src.first_rhs + rhs, nth = number / src.ncls, noise = src.first_noise + nth;
+    const int cls = (int)(number - nth * src.ncls);
     if (src.kind == DL_SRC_POINT) {
 #pragma unroll
         for (int e = 0; e < 12; ++e) eta[e] = {(lex == src.point_site && e == cls) ? 1.0 : 0.0, 0.0};
         return;
     }
     const double amp = 0.70710678118654752440;  // 1/sqrt(2)
-    if ((src.scheme & DL_DIL_TIME) && st.t != (int)(src.noise[rhs] % src.T)) {
+    if ((src.scheme & DL_DIL_TIME) && st.t != (int)(noise % src.T)) {
 #pragma unroll
         for (int e = 0; e < 12; ++e) eta[e] = {0.0, 0.0};
         return;
     }
-    const uint64_t base = ((uint64_t)src.noise[rhs] * (uint64_t)src.V + (uint64_t)lex) * 12ull;
+    const uint64_t base = ((uint64_t)noise * (uint64_t)src.V + (uint64_t)lex) * 12ull;
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -76,8 +77,10 @@ __device__ __forceinline__ void source_site(const SourceSpec &src, int rhs, cons
 // ---------------------------------------------------------------- kernels
 
 template <typename S>
-__global__ __launch_bounds__(BS) void source_kernel(Field dst, int parity, SourceSpec src, Geom g)
+__global__ __launch_bounds__(BS) void source_kernel(Field even, Field odd, SourceSpec src, Geom g)
 {
+    const int parity = blockIdx.z;
+    const Field dst = parity ? odd : even;
     using R = typename Fmt<S>::R;
     const int rhs = blockIdx.y;
     const int cb = blockIdx.x * BS + threadIdx.x;
@@ -146,28 +149,26 @@ __global__ __launch_bounds__(BS) void trace_kernel(Field se, Field so, SourceSpe
     }
 }
 
-// loops[n][g][t] = sum_d sum_{ab} Gamma_g[a][b] C[n*ncls + d][t][a][b]
-__global__ void gamma_contract_kernel(const double *C, int ncls, int T, const double *gam, const int *gidx,
-                                      int n_gamma, double *loops)
+// loops[n][g][t] = sum_d sum_{ab} Gamma_g[a][b] C[n*ncls + d][t][a][b], one thread per (g, t)
+__global__ __launch_bounds__(64) void gamma_contract_kernel(const double *C, int ncls, int T, GammaSet gam, double *loops)
 {
-    const int n = blockIdx.x;
-    for (int k = threadIdx.x; k < n_gamma * T; k += blockDim.x) {
-        const int gi = k / T, t = k - gi * T;
-        const double *G = gam + gidx[gi] * 32;
-        double re = 0, im = 0;
-        for (int d = 0; d < ncls; ++d) {
-            const double *c = C + (((int64_t)n * ncls + d) * T + t) * 32;
-            for (int ab = 0; ab < 16; ++ab) {
-                const double gr = G[2 * ab], gi2 = G[2 * ab + 1];
-                re += gr * c[2 * ab] - gi2 * c[2 * ab + 1];
-                im += gr * c[2 * ab + 1] + gi2 * c[2 * ab];
-            }
+    const int n = blockIdx.x, k = blockIdx.y * 64 + threadIdx.x;
+    if (k >= gam.n * T) return;
+    const int gi = k / T, t = k - gi * T;
+    double re = 0, im = 0;
+    for (int d = 0; d < ncls; ++d) {
+        const double *c = C + (((int64_t)n * ncls + d) * T + t) * 32;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const double *z = c + 2 * (4 * a + gam.col[gi][a]);
+            const double gr = gam.re[gi][a], gim = gam.im[gi][a];
+            re += gr * z[0] - gim * z[1];
+            im += gr * z[1] + gim * z[0];
         }
-        loops[(((int64_t)n * n_gamma + gi) * T + t) * 2] = re;
-        loops[(((int64_t)n * n_gamma + gi) * T + t) * 2 + 1] = im;
     }
+    loops[(((int64_t)n * gam.n + gi) * T + t) * 2] = re;
+    loops[(((int64_t)n * gam.n + gi) * T + t) * 2 + 1] = im;
 }
-
 
 // Gauge-covariant Gaussian smearing of quark fields (Section 2), one step on
 // the output parity p:
@@ -472,16 +473,18 @@ __global__ __launch_bounds__(256) void corr_kernel(const double *lb, const doubl
 
 // dst(x) = A_{n,t(x)} eta(x): the source gamma5 sum_g W[n][g][t] Gamma_g^+ eta of
 // the adjoint solve of noise n, with A as [noise][T][4][4] complex (row a, column b)
-__global__ __launch_bounds__(BS) void adjoint_source_kernel(Field dst, int parity, SourceSpec src, Geom g,
-                                                            const double *A, int64_t first_noise)
+__global__ __launch_bounds__(BS) void adjoint_source_kernel(Field even, Field odd, SourceSpec src, Geom g,
+                                                            const double *A)
 {
+    const int parity = blockIdx.z;
+    const Field dst = parity ? odd : even;
     const int rhs = blockIdx.y;
     const int cb = blockIdx.x * BS + threadIdx.x;
     if (cb >= g.Vh) return;
     const Site s = decode(g, cb, parity);
     cx<double> eta[12];
     source_site(src, rhs, s, lex_index(g, s), eta);
-    const double *At = A + ((src.noise[rhs] - first_noise) * g.T + s.t) * 32;
+    const double *At = A + ((src.first_rhs + rhs) / src.ncls * g.T + s.t) * 32;
     cx<double> v[12];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -658,11 +661,11 @@ double field_bytes(int prec, int64_t Vh, int nrhs)
 
 }  // namespace
 
-void k_source(int prec, Field dst, int parity, const SourceSpec &src, const Geom &g, int nrhs, hipStream_t s)
+void k_source(int prec, Field even, Field odd, const SourceSpec &src, const Geom &g, int nrhs, hipStream_t s)
 {
-    ProfScope ps(PROF_TRACE, field_bytes(prec, g.Vh, nrhs), s);
-    dim3 grid((g.Vh + BS - 1) / BS, nrhs);
-    DL_DISPATCH(prec, source_kernel, grid, dim3(BS), 0, s, dst, parity, src, g);
+    ProfScope ps(PROF_TRACE, 2 * field_bytes(prec, g.Vh, nrhs), s);
+    dim3 grid((g.Vh + BS - 1) / BS, nrhs, 2);
+    DL_DISPATCH(prec, source_kernel, grid, dim3(BS), 0, s, even, odd, src, g);
 }
 
 void k_trace(int prec, Field se, Field so, const SourceSpec &src, const Geom &g, int nrhs, double *C, hipStream_t s)
@@ -672,10 +675,10 @@ void k_trace(int prec, Field se, Field so, const SourceSpec &src, const Geom &g,
     DL_DISPATCH(prec, trace_kernel, grid, dim3(BS), 0, s, se, so, src, g, C);
 }
 
-void k_gamma_contract(const double *C, int n_noise, int ncls, int T, const double *gam, const int *gidx,
-                      int n_gamma, double *loops, hipStream_t s)
+void k_gamma_contract(const double *C, int n_noise, int ncls, int T, const GammaSet &gam, double *loops, hipStream_t s)
 {
-    hipLaunchKernelGGL(gamma_contract_kernel, dim3(n_noise), dim3(128), 0, s, C, ncls, T, gam, gidx, n_gamma, loops);
+    hipLaunchKernelGGL(gamma_contract_kernel, dim3(n_noise, (gam.n * T + 63) / 64), dim3(64), 0, s, C, ncls, T, gam,
+                       loops);
 }
 
 void k_smear(const void *links, int recon, Field ine, Field ino, Field oute, Field outo, const Geom &g, int nrhs,
@@ -767,12 +770,12 @@ void k_correlator(const double *lb, const double *la, double *sb, double *sa, in
     hipLaunchKernelGGL(corr_kernel, dim3(T), dim3(256), 0, s, lb, la, sb, sa, n, T, norm, out);
 }
 
-void k_adjoint_source(Field dst, int parity, const SourceSpec &src, const Geom &g, int nrhs, const double *A,
-                      int64_t first_noise, hipStream_t s)
+void k_adjoint_source(Field even, Field odd, const SourceSpec &src, const Geom &g, int nrhs, const double *A,
+                      hipStream_t s)
 {
-    ProfScope ps(PROF_TRACE, field_bytes(P64, g.Vh, nrhs), s);
-    dim3 grid((g.Vh + BS - 1) / BS, nrhs);
-    hipLaunchKernelGGL(adjoint_source_kernel, grid, dim3(BS), 0, s, dst, parity, src, g, A, first_noise);
+    ProfScope ps(PROF_TRACE, 2 * field_bytes(P64, g.Vh, nrhs), s);
+    dim3 grid((g.Vh + BS - 1) / BS, nrhs, 2);
+    hipLaunchKernelGGL(adjoint_source_kernel, grid, dim3(BS), 0, s, even, odd, src, g, A);
 }
 
 void k_link_grad(Field se, Field so, Field ae, Field ao, const Geom &g, int nrhs, double kappa, double *grad,

@@ -68,6 +68,28 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+// A page-locked host buffer for what a call brings back: copies into it neither
+// stage nor wait.  Blocks are kept for later calls (up to a bound;
+// dl_cache_release frees them).
+struct PinBuf {
+    void *p = nullptr;
+    size_t bytes = 0, cap = 0;
+    hipStream_t stream = nullptr;
+    bool busy = false;  // copies enqueued and not waited for
+    PinBuf(size_t n, hipStream_t s);
+    PinBuf(const PinBuf &) = delete;
+    PinBuf &operator=(const PinBuf &) = delete;
+    ~PinBuf();
+    void fetch(const void *src, size_t n, size_t at);  // device to offset `at`
+    void wait()
+    {
+        if (busy) DL_HIP(hipStreamSynchronize(stream));
+        busy = false;
+    }
+    template <typename T>
+    T *as() const { return static_cast<T *>(p); }
+};
+
 // The stream of the entry point running on this thread, for the duration of
 // the call: a device buffer released meanwhile enters the memory cache with an
 // event recorded on it, instead of a device-wide synchronisation.
@@ -353,11 +375,11 @@ struct SourceSpec {
     int64_t V;
     int T;            // time extent (time dilution: noise n lives on timeslice n mod T)
     int point_site;
-    const int64_t *noise;  // [nrhs] noise number of each right-hand side (device)
-    const int *cls;        // [nrhs] dilution class (device); point: 3*spin + colour
+    int64_t first_noise, first_rhs;  // right-hand side r is number first_rhs + r of the description:
+    int ncls;                        // its noise and its class (point: 3*spin + colour) by division by ncls
     Field xe = {nullptr, nullptr}, xo = {nullptr, nullptr};  // SRC_STORED: FP64 source per parity
 };
-void k_source(int prec, Field dst, int parity, const SourceSpec &src, const Geom &g, int nrhs, hipStream_t s);
+void k_source(int prec, Field even, Field odd, const SourceSpec &src, const Geom &g, int nrhs, hipStream_t s);
 // C[rhs][t][4][4] (complex) = sum_{x in t} sum_c conj(eta_{a c}(x)) s_{b c}(x)
 void k_trace(int prec, Field se, Field so, const SourceSpec &src, const Geom &g, int nrhs, double *C,
              hipStream_t s);
@@ -382,11 +404,15 @@ void eta_prime_fit(const double *d, const double *c, int ncfg, int T, double m_p
                    double *params, double *errors, double *chi2);
 void k_correlator(const double *lb, const double *la, double *sb, double *sa, int n, int T, double norm, double *out,
                   hipStream_t s);
-void k_gamma_contract(const double *C, int n_noise, int ncls, int T, const double *gam, const int *gidx,
-                      int n_gamma, double *loops, hipStream_t s);
+struct GammaSet {  // up to 16 Gammas: the non-zero entry of each row, its column and value (re, im in -1, 0, 1)
+    int n;
+    int8_t col[16][4], re[16][4], im[16][4];
+};
+void k_gamma_contract(const double *C, int n_noise, int ncls, int T, const GammaSet &gam, double *loops,
+                      hipStream_t s);
 // adjoint source dst(x) = A[noise - first_noise][t(x)] eta(x), A as [noise][T][4][4] complex (FP64 field)
-void k_adjoint_source(Field dst, int parity, const SourceSpec &src, const Geom &g, int nrhs, const double *A,
-                      int64_t first_noise, hipStream_t s);
+void k_adjoint_source(Field even, Field odd, const SourceSpec &src, const Geom &g, int nrhs, const double *A,
+                      hipStream_t s);
 // grad [4][V][3][3] complex += link gradient of Re sum conj(W) L from forward
 // solutions s and adjoint solutions a' (a = gamma5 a'), all FP64 parity fields
 void k_link_grad(Field se, Field so, Field ae, Field ao, const Geom &g, int nrhs, double kappa, double *grad,

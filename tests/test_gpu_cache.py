@@ -39,3 +39,36 @@ def test_cached_workspaces_repeat_bit_for_bit(dl, dev):
     dl.dl_cache_release()
     last4, _ = dl.loops(G, 0.124, src4, gam, prm)
     assert np.array_equal(last4, fresh4)
+
+
+def test_full_cache_makes_room_for_the_shapes_in_use(dl, dev):
+    """A cap that holds one shape's workspaces but not two: the second shape's blocks take the place of the first's
+    (the cap is never exceeded, and a repeated call adds nothing), and both shapes' results stay the same."""
+    dims = (6, 4, 6, 10)
+    U = synth.gauge_field(dims, 0.5, seed=611)
+    G = dl.Gauge(dl.Lattice(dims, 1), U, precs=(dl.DL_F64, dl.DL_F32))
+    prm = dl.solve_params(prec=dl.DL_F32, tol=1e-10, maxiter=2000)
+    big, small = dl.z2_sources(6110, 8), dl.z2_sources(6110, 3)
+
+    def run(src):
+        return dl.loops(G, 0.124, src, [0, 15], prm)[0]
+
+    dl.dl_cache_release()
+    first = run(small)
+    one = dl.dl_cache_bytes()
+    dl.dl_cache_release()
+    ref = run(big)
+    limit = dl.dl_cache_bytes()
+    assert 0 < one < limit
+    try:
+        dl.dl_cache_set_limit(limit)
+        assert np.array_equal(run(small), first)
+        held = dl.dl_cache_bytes()
+        # the larger blocks of the earlier shape went, longest unused first, as far as the cap asked
+        assert held <= limit
+        assert np.array_equal(run(small), first) and dl.dl_cache_bytes() == held
+        assert np.array_equal(run(big), ref) and dl.dl_cache_bytes() <= limit
+    finally:
+        dl.dl_cache_set_limit(64 << 30)
+        dl.dl_cache_release()
+    assert dl.dl_cache_bytes() == 0
