@@ -424,6 +424,11 @@ __global__ __launch_bounds__(256) void dslash_kernel(Segs<DKArgs> B)
 // neighbour spinors they share are then fetched into that XCD's L2 once.
 // The partial sums of a reducing epilogue are per wavefront, i.e. per
 // (right-hand side, 64-site block).
+// A lattice with fewer site blocks than the chip holds gives each of them to
+// `split` workgroups, neighbours on one XCD, which deal its right-hand sides
+// out among them (workgroup s of a site block takes wavefronts s * LANES .. of
+// split * LANES): the walk is then as much shorter, for as many stagings of
+// the block's links.
 constexpr int LDS_SITES = 64;
 
 // Whether the LDS holds the links expanded (9 complex numbers per link in the
@@ -559,7 +564,7 @@ __device__ __forceinline__ void write_block_partials(const DKArgs &a, int r, int
 }
 
 template <typename S, int NE, bool DAG, int EPI, int LANES, int OCC>
-__global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArgs> B, int rb)
+__global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArgs> B, int rb, int split)
 {
     using R = typename Fmt<S>::R;
     using E = typename Fmt<S>::E;
@@ -603,8 +608,10 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
     const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
     const int nbx = gridDim.x / 8 + (xcd < (int)(gridDim.x % 8) ? 1 : 0);
     const int myreg = nreg / 8 + (xcd < nreg % 8 ? 1 : 0);
-    const int cnt = myreg * rb;
-    for (int it = j; it < cnt; it += nbx) {
+    const int cnt = myreg * rb * split;
+    const int walkers = LANES * split;  // wavefronts that share a site block's right-hand sides
+    for (int its = j; its < cnt; its += nbx) {
+        const int it = its / split, me = (its - it * split) * LANES + w;
         const int ri = it / rb;
         const int item = (xcd + 8 * ri) * rb + (it - ri * rb);
         if (item >= total) continue;  // uniform across the block
@@ -671,12 +678,12 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
             }
         };
         unsigned nlive = 0;
-        // Wavefront w takes right-hand sides w, w + LANES, ...  The flags of its
+        // Wavefront `me` takes right-hand sides me, me + walkers, ...  The flags of its
         // next 64 are read once, one per lane, into a wave-uniform mask, so the
         // walk itself reads no flag: a flag load inside it would wait for the
         // previous right-hand side's stores.
-        for (int r0 = w; r0 < a.nrhs; r0 += 64 * LANES) {
-            const int rl = r0 + sl * LANES;
+        for (int r0 = me; r0 < a.nrhs; r0 += 64 * walkers) {
+            const int rl = r0 + sl * walkers;
             const bool on = rl < a.nrhs && (a.active == nullptr || a.active[rl] != 0);
             uint64_t m = __ballot(on);
             nlive += (unsigned)__popcll(m);
@@ -691,7 +698,7 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
                 // (without the fences the compiler issues all eight hops'
                 // loads at once and spills).
                 if (m == 0) continue;
-                int r = r0 + __builtin_ctzll(m) * LANES;
+                int r = r0 + __builtin_ctzll(m) * walkers;
                 m &= m - 1;
                 __amdgpu_buffer_rsrc_t rin = spinor_rsrc<S>(a.in, g.Vh, r);
                 // hop k's neighbour goes to buf[k % NBUF]: NBUF divides 8, so
@@ -702,7 +709,7 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
                 for (int k = 0; k < PF; ++k) load_hop(rin, r, k, buf[k]);
                 while (true) {
                     const bool more = m != 0;
-                    const int rn = more ? r0 + __builtin_ctzll(m) * LANES : r;
+                    const int rn = more ? r0 + __builtin_ctzll(m) * walkers : r;
                     m &= m - 1;
                     const __amdgpu_buffer_rsrc_t rin_n = spinor_rsrc<S>(a.in, g.Vh, rn);
                     double part[NP > 0 ? NP : 1];
@@ -738,7 +745,7 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
                 }
             } else {
                 while (m != 0) {
-                    const int r = r0 + __builtin_ctzll(m) * LANES;
+                    const int r = r0 + __builtin_ctzll(m) * walkers;
                     m &= m - 1;
                     const __amdgpu_buffer_rsrc_t rin = spinor_rsrc<S>(a.in, g.Vh, r);
                     double part[NP > 0 ? NP : 1];

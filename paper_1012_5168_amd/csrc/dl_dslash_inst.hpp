@@ -9,30 +9,30 @@
 namespace dl {
 
 template <typename S, int NE, bool DAG, int EPI, int LANES>
-static void dslash_go_lds(const Segs<DKArgs> &B, int occ, int grid, int rb, hipStream_t s)
+static void dslash_go_lds(const Segs<DKArgs> &B, int occ, int grid, int rb, int split, hipStream_t s)
 {
     if (occ == 1)
-        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 1>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb);
+        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 1>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb, split);
     else if (occ == 2)
-        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 2>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb);
+        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 2>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb, split);
     else
-        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 0>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb);
+        hipLaunchKernelGGL((dslash_lds_kernel<S, NE, DAG, EPI, LANES, 0>), dim3(grid), dim3(LANES * LDS_SITES), 0, s, B, rb, split);
 }
 
 // kind 1 (LDS-link kernel): nr wavefronts per block, `occ` wavefronts per SIMD
 // at most (0: as compiled), regions of rb blocks; kind 0 (item kernel): nr
 // right-hand sides per thread, bs sites per block
 template <typename S, int NE, bool DAG, int EPI>
-static void dslash_go_nr(const Segs<DKArgs> &B, int kind, int nr, int grid, int bs, int rb, hipStream_t s)
+static void dslash_go_nr(const Segs<DKArgs> &B, int kind, int nr, int grid, int bs, int rb, int split, hipStream_t s)
 {
     if constexpr (lds_link_bytes<S, NE>() <= LDS_WORKGROUP_BYTES) {
         if (kind == 1) {
             if (nr == 4)
-                dslash_go_lds<S, NE, DAG, EPI, 4>(B, bs, grid, rb, s);
+                dslash_go_lds<S, NE, DAG, EPI, 4>(B, bs, grid, rb, split, s);
             else if (nr == 2)
-                dslash_go_lds<S, NE, DAG, EPI, 2>(B, bs, grid, rb, s);
+                dslash_go_lds<S, NE, DAG, EPI, 2>(B, bs, grid, rb, split, s);
             else
-                dslash_go_lds<S, NE, DAG, EPI, 1>(B, bs, grid, rb, s);
+                dslash_go_lds<S, NE, DAG, EPI, 1>(B, bs, grid, rb, split, s);
             return;
         }
     }
@@ -43,17 +43,17 @@ static void dslash_go_nr(const Segs<DKArgs> &B, int kind, int nr, int grid, int 
 }
 
 template <typename S, int NE, bool DAG>
-static void dslash_go_epi(const Segs<DKArgs> &B, int epi, int kind, int nr, int grid, int bs, int rb, hipStream_t s)
+static void dslash_go_epi(const Segs<DKArgs> &B, int epi, int kind, int nr, int grid, int bs, int rb, int split, hipStream_t s)
 {
     switch (epi) {
-    case EPI_PLAIN: dslash_go_nr<S, NE, DAG, EPI_PLAIN>(B, kind, nr, grid, bs, rb, s); break;
-    case EPI_XPAY: dslash_go_nr<S, NE, DAG, EPI_XPAY>(B, kind, nr, grid, bs, rb, s); break;
-    case EPI_XPAY_DOT: dslash_go_nr<S, NE, DAG, EPI_XPAY_DOT>(B, kind, nr, grid, bs, rb, s); break;
-    case EPI_XPAY_TS: dslash_go_nr<S, NE, DAG, EPI_XPAY_TS>(B, kind, nr, grid, bs, rb, s); break;
-    case EPI_XPAY_NRM: dslash_go_nr<S, NE, DAG, EPI_XPAY_NRM>(B, kind, nr, grid, bs, rb, s); break;
-    case EPI_XMY_NRM: dslash_go_nr<S, NE, DAG, EPI_XMY_NRM>(B, kind, nr, grid, bs, rb, s); break;
+    case EPI_PLAIN: dslash_go_nr<S, NE, DAG, EPI_PLAIN>(B, kind, nr, grid, bs, rb, split, s); break;
+    case EPI_XPAY: dslash_go_nr<S, NE, DAG, EPI_XPAY>(B, kind, nr, grid, bs, rb, split, s); break;
+    case EPI_XPAY_DOT: dslash_go_nr<S, NE, DAG, EPI_XPAY_DOT>(B, kind, nr, grid, bs, rb, split, s); break;
+    case EPI_XPAY_TS: dslash_go_nr<S, NE, DAG, EPI_XPAY_TS>(B, kind, nr, grid, bs, rb, split, s); break;
+    case EPI_XPAY_NRM: dslash_go_nr<S, NE, DAG, EPI_XPAY_NRM>(B, kind, nr, grid, bs, rb, split, s); break;
+    case EPI_XMY_NRM: dslash_go_nr<S, NE, DAG, EPI_XMY_NRM>(B, kind, nr, grid, bs, rb, split, s); break;
     case EPI_CG_R:  // only the adjoint hop of the normal equations uses it
-        if constexpr (DAG) dslash_go_nr<S, NE, DAG, EPI_CG_R>(B, kind, nr, grid, bs, rb, s);
+        if constexpr (DAG) dslash_go_nr<S, NE, DAG, EPI_CG_R>(B, kind, nr, grid, bs, rb, split, s);
         break;
     default: break;
     }
@@ -116,28 +116,40 @@ void launch_dslash_t(const DslashCall *c, int nseg, int kind, int nr, int bs, in
         B.prefix[k + 1] = B.prefix[k] + a.nblk * groups;
     }
     const int total = B.prefix[nseg];
-    int grid, rb = 0;
+    int grid, rb = 0, split = 1;
     if (kind == 1) {
+        // Workgroups per site block: as many as the chip holds at once (by their
+        // LDS), while every wavefront has a right-hand side; with the chip full
+        // the stagings would only add traffic.  One workgroup per block left most
+        // of the chip idle on 64 blocks: loops of 48 right-hand sides in mixed
+        // precision at 8^3 x 16 took 6.25 ms, 5.72 dealt out; a gradient of 24 FP64
+        // ones there 17.3 and 16.4 ms; 12 mixed solves at 12^3 x 24 4.82 and 4.69.
+        int nrhs = 0;
+        for (int k = 0; k < nseg; ++k) nrhs = std::max(nrhs, c[k].nrhs);
+        const int resident = 256 * (LDS_WORKGROUP_BYTES / lds_link_block_bytes(c[0].prec, c[0].recon));
+        split = std::max(1, std::min(resident / total, nrhs / nr));
+        const int walk = (nrhs + nr * split - 1) / (nr * split);
+        split = (nrhs + nr * walk - 1) / (nr * walk);  // the fewest for a walk of this length
         rb = persistent > 0 ? persistent : 64;
         // a region is at most an XCD's share, so that every XCD gets work on
         // lattices of fewer than 8 rb site blocks
         rb = std::max(1, std::min(rb, (total + 7) / 8));
         const int nreg = (total + rb - 1) / rb;
-        grid = 8 * ((nreg + 7) / 8) * rb;
+        grid = 8 * ((nreg + 7) / 8) * rb * split;
     } else {
         grid = (persistent > 0 && total > persistent) ? persistent : total;
     }
     const DslashCall &c0 = c[0];
     if (c0.recon == 12) {
         if (c0.dag)
-            dslash_go_epi<S, 6, true>(B, c0.epi, kind, nr, grid, bs, rb, s);
+            dslash_go_epi<S, 6, true>(B, c0.epi, kind, nr, grid, bs, rb, split, s);
         else
-            dslash_go_epi<S, 6, false>(B, c0.epi, kind, nr, grid, bs, rb, s);
+            dslash_go_epi<S, 6, false>(B, c0.epi, kind, nr, grid, bs, rb, split, s);
     } else {
         if (c0.dag)
-            dslash_go_epi<S, 9, true>(B, c0.epi, kind, nr, grid, bs, rb, s);
+            dslash_go_epi<S, 9, true>(B, c0.epi, kind, nr, grid, bs, rb, split, s);
         else
-            dslash_go_epi<S, 9, false>(B, c0.epi, kind, nr, grid, bs, rb, s);
+            dslash_go_epi<S, 9, false>(B, c0.epi, kind, nr, grid, bs, rb, split, s);
     }
 }
 

@@ -20,7 +20,7 @@
 // with its output redirected to a scratch field of the same size); a
 // candidate replaces the default only if it is 3%
 // faster, and the result is kept in memory and in a text cache file
-// (DL_TUNE_CACHE, default ~/.cache/dloops/tune_gfx950_v5.txt).
+// (DL_TUNE_CACHE, default ~/.cache/dloops/tune_gfx950_v6.txt).
 // DL_TUNE=0 disables tuning and uses the default: the LDS-link kernel with 2
 // wavefronts, one wavefront per SIMD and regions of 64 blocks where its links
 // fit in LDS (FP64 with 12-parameter links: 1 wavefront per block, four
@@ -75,7 +75,7 @@ std::string cache_path()
 {
     if (const char *p = std::getenv("DL_TUNE_CACHE")) return p;
     const char *home = std::getenv("HOME");
-    return std::string(home ? home : "/tmp") + "/.cache/dloops/tune_gfx950_v5.txt";
+    return std::string(home ? home : "/tmp") + "/.cache/dloops/tune_gfx950_v6.txt";
 }
 
 // DL_TUNE: unset or anything else = tune; "0" = default; "item" / "lds" =

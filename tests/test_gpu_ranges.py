@@ -154,3 +154,28 @@ def test_solve_of_small_lattices(dl, dev, dims, recon, prec):
         x, st = dl.solve(G, kappa, to_dev(b[:1], dev), dl.solve_params(prec=prec, tol=1e-11, maxiter=3))
         rr = np.linalg.norm(b[0] - oracle.apply_m(U, from_dev(x)[0], dims, kappa, tap)) / np.linalg.norm(b[0])
         assert st[0][0] == dl.DL_ENOCONV and st[0][1] == 3 and abs(rr - st[0][3]) <= 1e-6 * rr
+
+
+# 12 and 1 site blocks, the last of 16 and 32 sites: 3, 24 and 70 workgroups per site block of one right-hand side each,
+# the same with walks cut short, and one workgroup per block where the wavefronts are as many as the right-hand sides
+@pytest.mark.parametrize("cfg", ["cfg:1:1:0:64", "cfg:1:2:0:32", "cfg:1:4:0:128"])
+@pytest.mark.parametrize("dims,nrhs", [((6, 4, 6, 10), 3), ((6, 4, 6, 10), 70), ((4, 4, 2, 2), 24), ((16, 16, 16, 30), 9)])
+def test_hops_dealt_out_over_workgroups(dl, dev, monkeypatch, dims, nrhs, cfg):
+    monkeypatch.setenv("DL_TUNE", cfg)
+    U = synth.gauge_field(dims, 0.4, seed=921)
+    par = oracle.parity(dims)
+    kappa = 0.131
+    G = dl.Gauge(dl.Lattice(dims, 1), U, precs=(dl.DL_F64, dl.DL_F32))
+    psi = synth.random_spinor(dims, nrhs, seed=922)
+    out = from_dev(dl.apply(G, kappa, dl.DL_OP_MHAT, to_dev(psi, dev)))
+    for r in {0, 1, nrhs // 2, nrhs - 2, nrhs - 1}:
+        pe = psi[r].copy()
+        pe[par == 1] = 0
+        ref = oracle.apply_mhat(U, pe, dims, kappa, 1)
+        ref[par == 1] = 0
+        assert np.max(np.abs(out[r] - ref)) <= 1e-13 * np.max(np.abs(ref)), r
+    x, st = dl.solve(G, kappa, to_dev(psi, dev), dl.solve_params(prec=dl.DL_F32, tol=1e-10, maxiter=2000))
+    x = from_dev(x)
+    for r in {0, nrhs // 2, nrhs - 1}:
+        assert st[r][0] == dl.DL_OK
+        assert oracle_residual(U, x[r], psi[r], dims, kappa) <= 1.5e-10
