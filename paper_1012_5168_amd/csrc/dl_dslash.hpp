@@ -60,27 +60,28 @@ __device__ __forceinline__ void project(const cx<R> p[12], cx<R> h[6])
     }
 }
 
-// acc += [g ; s A_mu^+ g]
-template <typename R, int MU, int SG>
+// acc += [g ; s A_mu^+ g], or acc = with FIRST (the walk's first hop: 24 additions to zero less)
+template <typename R, int MU, int SG, bool FIRST = false>
 __device__ __forceinline__ void reconstruct(cx<R> acc[12], const cx<R> g[6])
 {
     const R s = R(SG);
+    auto add = [](cx<R> &a, const cx<R> &b) { a = FIRST ? b : a + b; };
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        acc[c] = acc[c] + g[c];
-        acc[3 + c] = acc[3 + c] + g[3 + c];
+        add(acc[c], g[c]);
+        add(acc[3 + c], g[3 + c]);
         if constexpr (MU == 0) {  // A^+ = i sigma_1: A^+ g = i (g1, g0)
-            acc[6 + c] = acc[6 + c] + s * times_i(g[3 + c]);
-            acc[9 + c] = acc[9 + c] + s * times_i(g[c]);
+            add(acc[6 + c], s * times_i(g[3 + c]));
+            add(acc[9 + c], s * times_i(g[c]));
         } else if constexpr (MU == 1) {  // A^+ = i sigma_2: A^+ g = (g1, -g0)
-            acc[6 + c] = acc[6 + c] + s * g[3 + c];
-            acc[9 + c] = acc[9 + c] - s * g[c];
+            add(acc[6 + c], s * g[3 + c]);
+            add(acc[9 + c], -s * g[c]);
         } else if constexpr (MU == 2) {  // A^+ = i sigma_3: A^+ g = (i g0, -i g1)
-            acc[6 + c] = acc[6 + c] + s * times_i(g[c]);
-            acc[9 + c] = acc[9 + c] - s * times_i(g[3 + c]);
+            add(acc[6 + c], s * times_i(g[c]));
+            add(acc[9 + c], -s * times_i(g[3 + c]));
         } else {
-            acc[6 + c] = acc[6 + c] + s * g[c];
-            acc[9 + c] = acc[9 + c] + s * g[3 + c];
+            add(acc[6 + c], s * g[c]);
+            add(acc[9 + c], s * g[3 + c]);
         }
     }
 }
@@ -108,32 +109,40 @@ __device__ __forceinline__ void colour_mul(const cx<R> u[9], const cx<R> h[6], c
 // One spatial hop (MU < 3) on a loaded neighbour spinor in the stored basis:
 // project with the projector (1 + SG g_MU), colour-multiply by U (forward)
 // or U^+ (backward), reconstruct into the accumulator.
-template <typename R, int MU, int SG, bool FWD>
+template <typename R, int MU, int SG, bool FWD, bool FIRST = false>
 __device__ __forceinline__ void hop_mul(const cx<R> u[9], const cx<R> psi[12], cx<R> acc[12])
 {
     static_assert(MU < 3, "temporal hops take one spin pair (hop_mul_t)");
     cx<R> h[6], gg[6];
     project<R, MU, -SG>(psi, h);
     colour_mul<R, FWD>(u, h, gg);
-    reconstruct<R, MU, -SG>(acc, gg);
+    reconstruct<R, MU, -SG, FIRST>(acc, gg);
 }
 
 // The spin pair a temporal projector (1 + SG g_4) keeps: 0 = upper, 1 = lower.
 template <int SG>
 constexpr int t_half() { return SG > 0 ? 0 : 1; }
 
-// One temporal hop: `half` is the spin pair t_half<SG>() of the neighbour and
-// coef = 2 b (the projector's 2 times the time-boundary sign).
+// One temporal hop: `half` is the spin pair t_half<SG>() of the neighbour.  The
+// projector's 2 times the time-boundary sign is in the link already (hop_mul_u;
+// a power of two, so that nothing rounds differently) or is given as coef = 2 b.
 template <typename R, int SG, bool FWD>
-__device__ __forceinline__ void hop_mul_t(const cx<R> u[9], const cx<R> half[6], R coef, cx<R> acc[12])
+__device__ __forceinline__ void hop_mul_u(const cx<R> u[9], const cx<R> half[6], cx<R> acc[12])
 {
-    cx<R> h[6], gg[6];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) h[e] = coef * half[e];
-    colour_mul<R, FWD>(u, h, gg);
+    cx<R> gg[6];
+    colour_mul<R, FWD>(u, half, gg);
     constexpr int o = 6 * t_half<SG>();
 #pragma unroll
     for (int e = 0; e < 6; ++e) acc[o + e] = acc[o + e] + gg[e];
+}
+
+template <typename R, int SG, bool FWD>
+__device__ __forceinline__ void hop_mul_t(const cx<R> u[9], const cx<R> half[6], R coef, cx<R> acc[12])
+{
+    cx<R> h[6];
+#pragma unroll
+    for (int e = 0; e < 6; ++e) h[e] = coef * half[e];
+    hop_mul_u<R, SG, FWD>(u, h, acc);
 }
 
 // Pin the accumulators: this forces a hop's arithmetic to finish before the
@@ -629,6 +638,9 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
         const Site s = decode(g, cb, p);
         int nb[8];
         neighbours(g, cb, s, nb);
+        // the temporal projectors' 2 times the time-boundary sign, taken into the
+        // links once per block instead of into every right-hand side's spinors
+        const R cf = g.tap && s.t + 1 == g.T ? R(-2) : R(2), cbk = g.tap && s.t == 0 ? R(-2) : R(2);
         __syncthreads();  // the previous item's links are no longer read
         for (int d = w; d < 8; d += LANES) {
             if (lds_tregs<S>() && d >= 6) continue;
@@ -638,8 +650,9 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
             if constexpr (lds_expanded<S, NE>()) {
                 cx<R> u[9];
                 load_link<S, NE>(a.links, g.Vh, mu, bwd ? q : p, lcb, u);
+                const R c = d < 6 ? R(1) : d == 6 ? cf : cbk;
 #pragma unroll
-                for (int e = 0; e < 9; ++e) lx[(d * 9 + e) * LDS_SITES + sl] = u[e];
+                for (int e = 0; e < 9; ++e) lx[(d * 9 + e) * LDS_SITES + sl] = c * u[e];
             } else {
 #pragma unroll
                 for (int e = 0; e < NE; ++e) lk[(d * NE + e) * LDS_SITES + sl] = src[(int64_t)e * g.Vh];
@@ -648,11 +661,14 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
         if constexpr (lds_tregs<S>()) {
             load_link<S, NE>(a.links, g.Vh, 3, p, cb, ut[0]);
             load_link<S, NE>(a.links, g.Vh, 3, q, nb[7], ut[1]);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                ut[0][e] = cf * ut[0][e];
+                ut[1][e] = cbk * ut[1][e];
+            }
         }
         __syncthreads();
 
-        const R bf = (g.tap && s.t + 1 == g.T) ? R(-1) : R(1);
-        const R bb = (g.tap && s.t == 0) ? R(-1) : R(1);
         // hop d's neighbour of right-hand side rr (resource rs) into dst
         auto load_hop = [&](__amdgpu_buffer_rsrc_t rs, int rr, int d, CxSpinor<R> &dst) {
             if (d < 6)
@@ -666,15 +682,21 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
         auto apply_hop = [&](int d, const CxSpinor<R> &src, cx<R> acc[12]) {
             cx<R> u[9];
             load_u(d, sl, u);
+            if constexpr (!lds_expanded<S, NE>() && !lds_tregs<S>()) {
+                if (d >= 6) {
+#pragma unroll
+                    for (int e = 0; e < 9; ++e) u[e] = (d == 6 ? cf : cbk) * u[e];
+                }
+            }
             switch (d) {
-            case 0: hop_mul<R, 0, SF, true>(u, src.v, acc); break;
+            case 0: hop_mul<R, 0, SF, true, true>(u, src.v, acc); break;
             case 1: hop_mul<R, 0, SB, false>(u, src.v, acc); break;
             case 2: hop_mul<R, 1, SF, true>(u, src.v, acc); break;
             case 3: hop_mul<R, 1, SB, false>(u, src.v, acc); break;
             case 4: hop_mul<R, 2, SF, true>(u, src.v, acc); break;
             case 5: hop_mul<R, 2, SB, false>(u, src.v, acc); break;
-            case 6: hop_mul_t<R, SF, true>(u, src.v, R(2) * bf, acc); break;
-            default: hop_mul_t<R, SB, false>(u, src.v, R(2) * bb, acc); break;
+            case 6: hop_mul_u<R, SF, true>(u, src.v, acc); break;
+            default: hop_mul_u<R, SB, false>(u, src.v, acc); break;
             }
         };
         unsigned nlive = 0;
@@ -715,9 +737,7 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
                     double part[NP > 0 ? NP : 1];
 #pragma unroll
                     for (int k = 0; k < (NP > 0 ? NP : 1); ++k) part[k] = 0.0;
-                    cx<R> acc[12];
-#pragma unroll
-                    for (int e = 0; e < 12; ++e) acc[e] = {R(0), R(0)};
+                    cx<R> acc[12];  // set by hop 0
                     EpiOps<R, EPI> ops;
 #pragma unroll
                     for (int d = 0; d < 8; ++d) {
@@ -751,9 +771,7 @@ __global__ __launch_bounds__(LDS_SITES *LANES) void dslash_lds_kernel(Segs<DKArg
                     double part[NP > 0 ? NP : 1];
 #pragma unroll
                     for (int k = 0; k < (NP > 0 ? NP : 1); ++k) part[k] = 0.0;
-                    cx<R> acc[12];
-#pragma unroll
-                    for (int e = 0; e < 12; ++e) acc[e] = {R(0), R(0)};
+                    cx<R> acc[12];  // set by hop 0
                     EpiOps<R, EPI> ops;
 #pragma unroll
                     for (int d = 0; d < 8; ++d) {
