@@ -226,8 +226,8 @@ typedef struct {
                                  batch's time divided by its right-hand sides) */
     double bytes;             /* algorithmic bytes of its field operands: every operand of every kernel
                                  its solve ran, moved once (per iteration 23 half fields for BiCGStab,
-                                 16 for CGNR, in the iteration precision; per reliable update up to 9
-                                 FP64 and 7 iteration-precision half fields; set-up and reconstruction); the
+                                 16 for CGNR, in the iteration precision; per reliable update up to 7
+                                 FP64 and 6 iteration-precision half fields; set-up and reconstruction); the
                                  links, shared by the batch, are not counted */
 } dl_solve_stats;
 

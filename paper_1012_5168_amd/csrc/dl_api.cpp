@@ -469,6 +469,8 @@ static void dslash_bytes(const DslashCall &c, double &per_rhs, double &links)
     if (c.epi != EPI_PLAIN) nfield += 1;                             // x
     if (c.epi == EPI_XPAY_DOT || c.epi == EPI_XMY_NRM || c.epi == EPI_XPAY_TS || c.epi == EPI_CG_R) nfield += 1;  // y
     per_rhs = nfield * field;
+    // in, x, y; r, p and rhat read, r and p written
+    if (c.epi == EPI_REPLACE) per_rhs = 3 * field + 5 * vh * (12 * (double)elem_bytes(c.lprec) + (c.lprec == P16 ? 4 : 0));
 }
 
 bool dslash_lds_ok(int prec, int recon) { return lds_link_block_bytes(prec, recon) <= LDS_WORKGROUP_BYTES; }
@@ -1016,7 +1018,7 @@ VSeg vs(std::initializer_list<Field> f, int64_t Vh, int n, const int *mask = nul
     VSeg a;
     int k = 0;
     for (const Field &x : f) a.f[k++] = x;
-    for (; k < 6; ++k) a.f[k] = NOF;
+    for (; k < 5; ++k) a.f[k] = NOF;
     a.st = st;
     a.mask = mask;
     a.Vh = Vh;
@@ -1352,8 +1354,7 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
                         }),
                         s);
     start_launch(prec, VS(P, [&](const Prob &p) {
-                     return vs({p.w->bhat.view(), p.w->r.view(), p.w->rh.view(), p.w->p.view(), p.w->x64.view(),
-                                mixed ? p.w->xlo.view() : NOF},
+                     return vs({p.w->bhat.view(), p.w->r.view(), p.w->rh.view(), p.w->p.view(), p.w->x64.view()},
                                p.Vh(), p.w->n, nullptr, p.w->parts.as<double>());
                  }),
                  s);
@@ -1389,7 +1390,8 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
         if (fc.upd > 0) {
             if (mixed)
                 fold_launch(prec, VS(P, [&](const Prob &p) {
-                                return vs({p.w->x64.view(), p.w->xlo.view()}, p.Vh(), p.w->n, upd(p));
+                                return vs({p.w->x64.view(), p.w->xlo.view()}, p.Vh(), p.w->n, upd(p), nullptr,
+                                          p.w->st.as<KState>());
                             }),
                             s);
             launch_dslash_batch(DS(P, [&](const Prob &p) {
@@ -1397,27 +1399,24 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
                                                  NOF, NOF, 1.0, p.w->n, nullptr, upd(p));
                                 }),
                                 s);
-            std::vector<int> nb64 = launch_dslash_batch(DS(P, [&](const Prob &p) {
-                                                            return dcall(p.c, P64, 0, false, EPI_XMY_NRM,
-                                                                         p.w->tmp64.view(), p.w->r64.view(),
-                                                                         p.w->bhat.view(), p.w->x64.view(),
-                                                                         p.kappa * p.kappa, p.w->n,
-                                                                         p.w->parts2.as<double>(), upd(p));
-                                                        }),
-                                                        s);
             // r <- the FP64 residual, p moved by the same difference (p holds
             // r + beta (p - omega v) already) and rho <- (rhat, r) of the new r
-            replace_launch(prec, VS(P, [&](const Prob &p) {
-                               return vs({p.w->r.view(), p.w->r64.view(), p.w->p.view(), p.w->rh.view()}, p.Vh(),
-                                         p.w->n, upd(p), p.w->parts.as<double>());
-                           }),
-                           s);
-            std::vector<SSeg> up = SS(P, blas_nb(P));
-            for (size_t k = 0; k < P.size(); ++k) {
-                up[k].parts2 = P[k].w->parts2.as<double>();
-                up[k].nblk2 = nb64[k];
-            }
-            scalar_launch(S_BICG_UPDATE, up, SParams{}, s);
+            const std::vector<int> nb64 =
+                launch_dslash_batch(DS(P, [&](const Prob &p) {
+                                        DslashCall d = dcall(p.c, P64, 0, false, EPI_REPLACE, p.w->tmp64.view(),
+                                                             p.w->r64.view(), p.w->bhat.view(), p.w->x64.view(),
+                                                             p.kappa * p.kappa, p.w->n, p.w->parts.as<double>(),
+                                                             upd(p));
+                                        d.lprec = prec;
+                                        d.lr = p.w->r.view();
+                                        d.lp = p.w->p.view();
+                                        d.lrh = p.w->rh.view();
+                                        return d;
+                                    }),
+                                    s);
+            SParams su;
+            su.mixed = mixed ? 1 : 0;
+            scalar_launch(S_BICG_UPDATE, SS(P, nb64), su, s);
             fc = count_flags(P, s);
             if (fc.restart > 0) {
                 // restart from the true residual: rhat = r, p = r
@@ -1585,14 +1584,14 @@ struct Stopwatch {
 // half fields in the iteration precision (the hops 2 + 4 + 2 + 4, the s
 // update 3, the fused x / r / p update 8); the truncated CGNR 16 (four hops
 // 2 + 3 + 2 + 4, the last of them forming q and updating r in its epilogue,
-// and the fused x and p update 5).  A reliable update moves 9 FP64 half
-// fields (2 for the fold, 2 + 4 for the FP64 residual hops, 1 for the
-// replacement of r) and 7 in the iteration precision (the fold 2, the
-// replacement of r and p with (rhat, r) 5); without iterations below FP64
-// there is no fold.  The set-up and the reconstruction of the odd sites move
+// and the fused x and p update 5).  A reliable update moves 7 FP64 half
+// fields (2 for the fold, 2 + 3 for the FP64 residual hops) and 6 in the
+// iteration precision (the fold 1, r, p and rhat in the replacing hop 5);
+// without iterations below FP64 there is no fold.  The iterate is zero, and not
+// read, at the start and after a fold.  The set-up and the reconstruction of the odd sites move
 // 10 FP64 half fields (source norms 2, prepared source 3, the start 2: the
-// prepared source read and x cleared, reconstruction 3) and 4 in the iteration
-// precision (r, rhat, p and the low-precision x written by the start).
+// prepared source read and x cleared, reconstruction 3) and 3 in the iteration
+// precision (r, rhat and p written by the start).
 double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
 {
     const double vh = (double)w.r.Vh;
@@ -1600,8 +1599,9 @@ double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
     if (cgnr) return k.iters * 16.0 * fb + 8.0 * fb;
     const double f8 = vh * 12.0 * 16.0;
     const bool mixed = w.prec != P64;
-    const double upd = mixed ? 9.0 * f8 + 7.0 * fb : 7.0 * f8 + 5.0 * fb;
-    return k.iters * 23.0 * fb + k.updates * upd + 10.0 * f8 + 4.0 * fb;
+    const double upd = mixed ? 7.0 * f8 + 6.0 * fb : 5.0 * f8 + 5.0 * fb;
+    const int fresh = std::min(k.iters, mixed ? std::max(1, k.updates) : 1);
+    return (k.iters * 23.0 - fresh) * fb + k.updates * upd + 10.0 * f8 + 3.0 * fb;
 }
 
 // The statistics of a solve: the solver states and, where asked for, the true

@@ -91,6 +91,7 @@ __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
     s.delta2 = p.delta2;
     s.maxiter = p.maxiter;
     s.done = b2 > 0 ? 0 : 1;
+    s.fresh = 1;
     a.st[rhs] = s;
     a.act[rhs] = b2 > 0 ? 1 : 0;
     a.upd[rhs] = 0;
@@ -123,6 +124,7 @@ __device__ void bicg_check(const SSeg &a, const SParams &p, int rhs)
     KState s = a.st[rhs];
     int act = 1, upd = a.upd[rhs];
     bicg_check_step(s, rr, s.delta2, s.maxiter, p.mixed, act, upd);
+    s.fresh = 0;
     a.act[rhs] = act;
     a.upd[rhs] = upd;
     a.st[rhs] = s;
@@ -154,21 +156,21 @@ __device__ void bicg_omega(const SSeg &a, int rhs)
     a.st[rhs] = s;
 }
 
-// partials [.., 2]: (rhat, r) of the replaced r; partials2 [.., 1]: |r|^2 of the
-// FP64 residual
-__device__ void bicg_update(const SSeg &a, int rhs)
+// partials [.., 3]: |r|^2 of the FP64 residual, (rhat, r) of the replaced r.  A
+// mixed-precision iterate was folded into the FP64 solution: it starts from zero.
+__device__ void bicg_update(const SSeg &a, const SParams &p, int rhs)
 {
     if (!a.upd[rhs]) {
         if (threadIdx.x == 0) a.restart[rhs] = 0;
         return;
     }
-    double rn[2], r2;
-    sum_parts<2>(a.parts, rhs, a.nblk, rn);
-    sum_parts<1>(a.parts2, rhs, a.nblk2, &r2);
+    double d[3];
+    sum_parts<3>(a.parts, rhs, a.nblk, d);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
     int act = a.act[rhs], restart;
-    bicg_update_step(s, rn, r2, s.maxiter, act, restart);
+    bicg_update_step(s, d + 1, d[0], s.maxiter, act, restart);
+    if (p.mixed) s.fresh = 1;
     a.act[rhs] = act;
     a.restart[rhs] = restart;
     a.upd[rhs] = 0;
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(64 * SCALAR_WAVES) void scalar_kernel(Segs<SSeg> B,
         else if constexpr (OP == S_BICG_ALPHA) bicg_alpha(a, rhs);
         else if constexpr (OP == S_BICG_OMEGA) bicg_omega(a, rhs);
         else if constexpr (OP == S_BICG_CHECK) bicg_check(a, p, rhs);
-        else if constexpr (OP == S_BICG_UPDATE) bicg_update(a, rhs);
+        else if constexpr (OP == S_BICG_UPDATE) bicg_update(a, p, rhs);
         else if constexpr (OP == S_CG_INIT) cg_init(a, p, rhs);
         else if constexpr (OP == S_CG_ALPHA) cg_alpha(a, rhs);
         else if constexpr (OP == S_CG_BETA) cg_beta(a, rhs);
@@ -295,7 +297,10 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
             const KState &k = a.st[rhs];
             const cx<R> alpha = ld_c<R>(k.alpha), omega = ld_c<R>(k.omega), beta = ld_c<R>(k.beta);
             cx<R> xv[12], sv[12], pv[12], tv[12], vv[12];
-            load_spinor<S, true>(a.f[0], Vh, rhs, cb, xv);
+            // an iterate that is still zero is neither cleared nor read
+#pragma unroll
+            for (int e = 0; e < 12; ++e) xv[e] = {R(0), R(0)};
+            if (!k.fresh) load_spinor<S, true>(a.f[0], Vh, rhs, cb, xv);
             load_spinor<S, true>(a.f[1], Vh, rhs, cb, sv);
             load_spinor<S, true>(a.f[2], Vh, rhs, cb, pv);
             load_spinor<S, true>(a.f[3], Vh, rhs, cb, tv);
@@ -387,7 +392,8 @@ __global__ __launch_bounds__(BS) void copy_kernel(Segs<VSeg> B)
     });
 }
 
-// f0 (FP64) += f1 (precision S); f1 = 0      (reliable update of x)
+// f0 (FP64) += f1 (precision S)      (reliable update of x; the next iteration takes
+// f1 as zero, KState.fresh)
 template <typename S>
 __global__ __launch_bounds__(BS) void fold_kernel(Segs<VSeg> B)
 {
@@ -401,58 +407,22 @@ __global__ __launch_bounds__(BS) void fold_kernel(Segs<VSeg> B)
         if (cb >= a.Vh) return;
         cx<double> xv[12];
         cx<R> lv[12];
-        load_spinor<double>(a.f[0], a.Vh, rhs, cb, xv);
-        load_spinor<S>(a.f[1], a.Vh, rhs, cb, lv);
+        if (a.st[rhs].fresh) return;  // no iteration since the last time
+        load_spinor<double, true>(a.f[0], a.Vh, rhs, cb, xv);
+        load_spinor<S, true>(a.f[1], a.Vh, rhs, cb, lv);
 #pragma unroll
         for (int e = 0; e < 12; ++e) {
             xv[e].re += (double)lv[e].re;
             xv[e].im += (double)lv[e].im;
-            lv[e] = {R(0), R(0)};
         }
         store_spinor<double, true>(a.f[0], a.Vh, rhs, cb, xv);
-        store_spinor<S, true>(a.f[1], a.Vh, rhs, cb, lv);
-    });
-}
-
-// f0 (r, precision S) = f1 (the FP64 residual); f2 (p, precision S) += f1 - old f0
-template <typename S>
-__global__ __launch_bounds__(BS) void replace_kernel(Segs<VSeg> B)
-{
-    using R = typename Fmt<S>::R;
-    __shared__ double red[2 * (BS / 64)];
-    for_each_item(B, [&](const VSeg &a, int item) {
-        const int nb = (int)((a.Vh + BS - 1) / BS);
-        const int rhs = item / nb, blk = item - rhs * nb;
-        if (masked_off(a.mask, rhs)) return;
-        count_live(a.live, blk);
-        const int64_t cb = (int64_t)blk * BS + threadIdx.x;
-        double part[2] = {0, 0};
-        if (cb < a.Vh) {
-            cx<R> rv[12], pv[12], hv[12];
-            cx<double> nv[12];
-            load_spinor<S>(a.f[0], a.Vh, rhs, cb, rv);
-            load_spinor<double>(a.f[1], a.Vh, rhs, cb, nv);
-            load_spinor<S>(a.f[2], a.Vh, rhs, cb, pv);
-            load_spinor<S>(a.f[3], a.Vh, rhs, cb, hv);
-#pragma unroll
-            for (int e = 0; e < 12; ++e) {
-                const cx<R> n = {R(nv[e].re), R(nv[e].im)};
-                pv[e] = pv[e] + (n - rv[e]);
-                rv[e] = n;
-                part[0] += (double)hv[e].re * rv[e].re + (double)hv[e].im * rv[e].im;
-                part[1] += (double)hv[e].re * rv[e].im - (double)hv[e].im * rv[e].re;
-            }
-            store_spinor<S, true>(a.f[0], a.Vh, rhs, cb, rv);
-            store_spinor<S, true>(a.f[2], a.Vh, rhs, cb, pv);
-        }
-        write_parts<2>(part, red, a.parts, rhs, nb, blk);
     });
 }
 
 // The start of BiCGStab from the FP64 prepared source f0: r (f1) = rhat (f2) =
-// p (f3) = f0 in the iteration precision, the FP64 solution f4 = 0 and below
-// FP64 the low-precision iterate f5 = 0; parts (rhat, r).  One pass instead of
-// two copies of r, a conversion, two clears and a dot product.
+// p (f3) = f0 in the iteration precision, the FP64 solution f4 = 0; parts
+// (rhat, r).  One pass instead of two copies of r, a conversion, a clear and a
+// dot product.
 template <typename S>
 __global__ __launch_bounds__(BS) void start_kernel(Segs<VSeg> B)
 {
@@ -480,11 +450,6 @@ __global__ __launch_bounds__(BS) void start_kernel(Segs<VSeg> B)
 #pragma unroll
             for (int e = 0; e < 12; ++e) bv[e] = {0.0, 0.0};
             store_spinor<double, true>(a.f[4], a.Vh, rhs, cb, bv);
-            if (a.f[5].d != nullptr) {
-#pragma unroll
-                for (int e = 0; e < 12; ++e) v[e] = {R(0), R(0)};
-                store_spinor<S, true>(a.f[5], a.Vh, rhs, cb, v);
-            }
         }
         write_parts<2>(part, red, a.parts, rhs, nb, blk);
     });
@@ -566,7 +531,7 @@ static int scalar_threads(int op, const std::vector<SSeg> &segs)
 {
     if (op == S_CG_INIT || op == S_CG_ALPHA || op == S_CG_BETA) return 64;
     int nblk = 0;
-    for (const SSeg &a : segs) nblk = std::max(nblk, std::max(a.nblk, a.nblk2));
+    for (const SSeg &a : segs) nblk = std::max(nblk, a.nblk);
     return nblk > 512 ? 64 * SCALAR_WAVES : 64;
 }
 
@@ -608,7 +573,7 @@ void vec_launch(int op, int prec, const std::vector<VSeg> &segs, hipStream_t s)
 
 void start_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s)
 {
-    const int n64 = 2, nlo = prec == P64 ? 3 : 4;
+    const int n64 = 2, nlo = 3;
     ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, n64) + vec_bytes(prec, segs, nlo), s);
     const std::vector<VSeg> sg = counted_segs(
         segs, ps, s, [&](int64_t Vh) { return n64 * field_rhs_bytes(P64, Vh) + nlo * field_rhs_bytes(prec, Vh); });
@@ -639,9 +604,9 @@ void copy_launch(int prec_dst, int prec_src, const std::vector<VSeg> &segs, hipS
 
 void fold_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s)
 {
-    ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, 2) + vec_bytes(prec, segs, 2), s);
+    ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, 2) + vec_bytes(prec, segs, 1), s);
     const std::vector<VSeg> sg = counted_segs(
-        segs, ps, s, [&](int64_t Vh) { return 2 * field_rhs_bytes(P64, Vh) + 2 * field_rhs_bytes(prec, Vh); });
+        segs, ps, s, [&](int64_t Vh) { return 2 * field_rhs_bytes(P64, Vh) + field_rhs_bytes(prec, Vh); });
     Segs<VSeg> B = make_segs(sg, vec_items);
     const int grid = grid_for(B.prefix[B.n], PERSIST);
     switch (prec) {
@@ -649,21 +614,6 @@ void fold_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s)
     case P32: hipLaunchKernelGGL(fold_kernel<float>, dim3(grid), dim3(BS), 0, s, B); break;
     case P16: hipLaunchKernelGGL(fold_kernel<__half>, dim3(grid), dim3(BS), 0, s, B); break;
     default: hipLaunchKernelGGL(fold_kernel<__hip_bfloat16>, dim3(grid), dim3(BS), 0, s, B); break;
-    }
-}
-
-void replace_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s)
-{
-    ProfScope ps(PROF_BLAS, vec_bytes(P64, segs, 1) + vec_bytes(prec, segs, 5), s);
-    const std::vector<VSeg> sg = counted_segs(
-        segs, ps, s, [&](int64_t Vh) { return field_rhs_bytes(P64, Vh) + 5 * field_rhs_bytes(prec, Vh); });
-    Segs<VSeg> B = make_segs(sg, vec_items);
-    const int grid = grid_for(B.prefix[B.n], PERSIST);
-    switch (prec) {
-    case P64: hipLaunchKernelGGL(replace_kernel<double>, dim3(grid), dim3(BS), 0, s, B); break;
-    case P32: hipLaunchKernelGGL(replace_kernel<float>, dim3(grid), dim3(BS), 0, s, B); break;
-    case P16: hipLaunchKernelGGL(replace_kernel<__half>, dim3(grid), dim3(BS), 0, s, B); break;
-    default: hipLaunchKernelGGL(replace_kernel<__hip_bfloat16>, dim3(grid), dim3(BS), 0, s, B); break;
     }
 }
 

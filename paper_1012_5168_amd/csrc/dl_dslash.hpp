@@ -33,6 +33,8 @@ struct DKArgs {
     const int *active;
     unsigned *live_count;
     const KState *st;
+    int lprec;     // EPI_REPLACE: out is r, p and rhat are
+    Field lp, lrh;
 };
 
 // h = psi_up + s A_mu psi_down (two spin components x three colours) with the
@@ -186,6 +188,7 @@ constexpr int nparts_c()
 {
     return EPI == EPI_XPAY_DOT ? 2
            : EPI == EPI_XPAY_TS ? 7
+           : EPI == EPI_REPLACE ? 3
            : (EPI == EPI_XPAY_NRM || EPI == EPI_XMY_NRM || EPI == EPI_CG_R) ? 1
                                                                            : 0;
 }
@@ -215,7 +218,8 @@ constexpr bool epi_reads_x()
 template <int EPI>
 constexpr bool epi_reads_y()
 {
-    return EPI == EPI_XPAY_DOT || EPI == EPI_XPAY_TS || EPI == EPI_XMY_NRM || EPI == EPI_CG_R;
+    return EPI == EPI_XPAY_DOT || EPI == EPI_XPAY_TS || EPI == EPI_XMY_NRM ||
+           EPI == EPI_CG_R || EPI == EPI_REPLACE;
 }
 template <typename R, int EPI>
 struct EpiOps {
@@ -230,6 +234,29 @@ __device__ __forceinline__ void epilogue_load(const DKArgs &a, int rhs, int64_t 
 {
     if constexpr (epi_reads_x<EPI>()) load_site<S, BUF>(a.x, a.g.Vh, rhs, cb, ops.x);
     if constexpr (epi_reads_y<EPI>()) load_site<S, BUF>(a.y, a.g.Vh, rhs, cb, ops.y);
+}
+
+// The reliable update at one site: r and p in the iteration precision S from the
+// FP64 residual n, p moved by the same difference as r.
+template <typename S>
+__device__ __forceinline__ void replace_site(const DKArgs &a, int rhs, int64_t cb, const cx<double> n[12], double &p1,
+                                             double &p2)
+{
+    using R = typename Fmt<S>::R;
+    cx<R> rv[12], pv[12], hv[12];
+    load_spinor<S, true>(a.out, a.g.Vh, rhs, cb, rv);
+    load_spinor<S, true>(a.lp, a.g.Vh, rhs, cb, pv);
+    load_spinor<S, true>(a.lrh, a.g.Vh, rhs, cb, hv);
+#pragma unroll
+    for (int e = 0; e < 12; ++e) {
+        const cx<R> w = {R(n[e].re), R(n[e].im)};
+        pv[e] = pv[e] + (w - rv[e]);
+        rv[e] = w;
+        p1 += (double)hv[e].re * w.re + (double)hv[e].im * w.im;
+        p2 += (double)hv[e].re * w.im - (double)hv[e].im * w.re;
+    }
+    store_spinor<S, true>(a.out, a.g.Vh, rhs, cb, rv);
+    store_spinor<S, true>(a.lp, a.g.Vh, rhs, cb, pv);
 }
 
 template <typename S, int EPI, bool NT>
@@ -247,7 +274,7 @@ __device__ __forceinline__ void epilogue_apply(const DKArgs &a, int rhs, int64_t
         cx<R> xv[12];
 #pragma unroll
         for (int e = 0; e < 12; ++e) xv[e] = ops.x[e];
-        if constexpr (EPI == EPI_XMY_NRM) {
+        if constexpr (EPI == EPI_XMY_NRM || EPI == EPI_REPLACE) {
 #pragma unroll
             for (int e = 0; e < 12; ++e) xv[e] = xv[e] - ops.y[e];
         }
@@ -299,13 +326,38 @@ __device__ __forceinline__ void epilogue_apply(const DKArgs &a, int rhs, int64_t
             }
         }
     }
+    if constexpr (EPI == EPI_REPLACE) {
+        // The FP64 residual goes straight into r and p, and is not stored: it
+        // crossed memory twice more when a pass of its own read it back (hop 1013
+        // and pass 731 us on 24 right-hand sides at 24^3 x 48; with the iterate
+        // neither cleared nor read after a fold, 24 mixed solves there 114.6 ->
+        // 109.8 ms).  The format is the same for the whole launch; a switch here
+        // saves a copy of the kernel per format.
+        if (valid) {
+            double p0 = 0.0, p1 = 0.0, p2 = 0.0;
+#pragma unroll
+            for (int e = 0; e < 12; ++e) p0 += o[e].re * o[e].re + o[e].im * o[e].im;
+            switch (a.lprec) {
+            case P64: replace_site<double>(a, rhs, cb, o, p1, p2); break;
+            case P32: replace_site<float>(a, rhs, cb, o, p1, p2); break;
+            case P16: replace_site<__half>(a, rhs, cb, o, p1, p2); break;
+            default: replace_site<__hip_bfloat16>(a, rhs, cb, o, p1, p2); break;
+            }
+            part[0] += p0;
+            part[1] += p1;
+            part[2] += p2;
+        }
+        return;
+    }
     if constexpr (EPI == EPI_XPAY_NRM || EPI == EPI_XMY_NRM || EPI == EPI_CG_R) {
         double p0 = 0.0;
 #pragma unroll
         for (int e = 0; e < 12; ++e) p0 += (double)o[e].re * o[e].re + (double)o[e].im * o[e].im;
         if (valid) part[0] += p0;
     }
-    if (valid) store_spinor<S, NT>(a.out, a.g.Vh, rhs, cb, o);
+    if constexpr (EPI != EPI_REPLACE) {
+        if (valid) store_spinor<S, NT>(a.out, a.g.Vh, rhs, cb, o);
+    }
 }
 
 template <typename S, int EPI, bool BUF = false, bool NT = false>

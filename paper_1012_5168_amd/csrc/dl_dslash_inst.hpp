@@ -55,6 +55,10 @@ static void dslash_go_epi(const Segs<DKArgs> &B, int epi, int kind, int nr, int 
     case EPI_CG_R:  // only the adjoint hop of the normal equations uses it
         if constexpr (DAG) dslash_go_nr<S, NE, DAG, EPI_CG_R>(B, kind, nr, grid, bs, rb, split, s);
         break;
+    case EPI_REPLACE:  // the FP64 residual of M only
+        if constexpr (std::is_same<S, double>::value && !DAG)
+            dslash_go_nr<S, NE, DAG, EPI_REPLACE>(B, kind, nr, grid, bs, rb, split, s);
+        break;
     default: break;
     }
 }
@@ -101,7 +105,7 @@ void launch_dslash_t(const DslashCall *c, int nseg, int kind, int nr, int bs, in
         a.g = c[k].g;
         a.parity = c[k].parity;
         a.in = c[k].in;
-        a.out = c[k].out;
+        a.out = c[k].epi == EPI_REPLACE ? c[k].lr : c[k].out;
         a.x = c[k].x;
         a.y = c[k].y;
         a.links = c[k].links;
@@ -112,6 +116,9 @@ void launch_dslash_t(const DslashCall *c, int nseg, int kind, int nr, int bs, in
         a.active = c[k].active;
         a.live_count = c[k].live_count;
         a.st = c[k].st;
+        a.lprec = c[k].lprec;
+        a.lp = c[k].lp;
+        a.lrh = c[k].lrh;
         const int groups = kind == 1 ? 1 : (c[k].nrhs + nr - 1) / nr;
         B.prefix[k + 1] = B.prefix[k] + a.nblk * groups;
     }

@@ -183,6 +183,9 @@ enum Epi {
     EPI_XMY_NRM = 5,   // out = x - y + a D in; partial |out|^2          [1 double]
     EPI_CG_R = 6,      // q = x + a D in; out = y - alpha q (out = y in place, alpha from
                        // the solver state); partial |out|^2; q itself is not stored   [1 double]
+    EPI_REPLACE = 7,   // FP64, the reliable update: n = x - y + a D in, not stored; in the iteration precision
+                       // r = n, p += n - old r, so that p = r + beta (p - omega v) holds for the
+                       // replaced r; partials |n|^2, (rhat, r)               [3 doubles]
 };
 
 inline int epi_nparts(int epi)
@@ -193,6 +196,7 @@ inline int epi_nparts(int epi)
     case EPI_XPAY_NRM: return 1;
     case EPI_XMY_NRM: return 1;
     case EPI_CG_R: return 1;
+    case EPI_REPLACE: return 3;
     default: return 0;
     }
 }
@@ -212,6 +216,8 @@ struct DslashCall {
     const int *active;    // per right-hand side flag or null
     unsigned *live_count = nullptr;  // profiling: live right-hand-side blocks
     const struct KState *st = nullptr;  // per right-hand side solver state (EPI_CG_R's alpha)
+    int lprec = 0;               // EPI_REPLACE: the iteration precision and its r, p, rhat (out is then
+    Field lr = {}, lp = {}, lrh = {};  // only what a timing of the launch may write)
 };
 
 // launch with the tuned (or default) configuration; returns the number of
@@ -275,13 +281,14 @@ struct KState {
     int nonfinite;
     int maxiter;
     int due;        // a reliable update is due (small-lattice solver)
+    int fresh;      // the iterate is zero, whatever its field holds
 };
 
 int blas_blocks(int64_t Vh);
 
 // Operands of a Krylov vector kernel for one segment (lattice).
 struct VSeg {
-    Field f[6];
+    Field f[5];
     const KState *st = nullptr;
     const int *mask = nullptr;  // per right-hand side flags selecting who acts (null = all)
     int64_t Vh = 0;
@@ -292,16 +299,12 @@ struct VSeg {
 enum VOp { V_BICG_S = 0, V_BICG_XRP, V_CG_P, V_ZERO, V_NORM2, V_RESTART };
 void vec_launch(int op, int prec, const std::vector<VSeg> &segs, hipStream_t s);
 void copy_launch(int prec_dst, int prec_src, const std::vector<VSeg> &segs, hipStream_t s);  // f0 = f1
-void fold_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s);   // f0 (FP64) += f1; f1 = 0
+void fold_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s);   // f0 (FP64) += f1, where f1 is not zero (KState.fresh)
 // measurement only: copy (mode 0) or read (mode 1) nwords 16-byte words with non-temporal accesses
 void stream_launch(int mode, const void *src, void *dst, int64_t nwords, hipStream_t s);
 void zero_launch(void *p, int64_t nwords, hipStream_t s);  // nwords 16-byte words
-// reliable update of the residual: f0 (r, precision prec) = f1 (FP64 residual), and the search
-// direction f2 (p, precision prec) += f1 - old f0, so that p = r + beta (p - omega v) holds for the
-// replaced r
-void replace_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s);
-// start of BiCGStab: f1 (r) = f2 (rhat) = f3 (p) = f0 (FP64) in precision prec, f4 (FP64 x) = 0, f5 (x in precision
-// prec, where set) = 0; parts (rhat, r)
+// start of BiCGStab: f1 (r) = f2 (rhat) = f3 (p) = f0 (FP64) in precision prec, f4 (FP64 x) = 0;
+// parts (rhat, r)
 void start_launch(int prec, const std::vector<VSeg> &segs, hipStream_t s);
 
 // Operands of a per-right-hand-side scalar kernel for one segment.
@@ -309,9 +312,8 @@ struct SSeg {
     KState *st = nullptr;
     int *act = nullptr, *upd = nullptr, *restart = nullptr;
     const int *mask = nullptr;
-    const double *parts = nullptr, *parts2 = nullptr;
+    const double *parts = nullptr;
     int nblk = 0;   // site blocks of the producing kernel (partials' middle extent)
-    int nblk2 = 0;  // the same for parts2
     int nrhs = 0;
     double *out = nullptr;
 };
@@ -325,7 +327,7 @@ enum SOp {
     S_BICG_ALPHA,     // parts: (rhat, v)
     S_BICG_OMEGA,     // parts: (t, s), |t|^2, (rhat, t), (rhat, s): omega, rho, beta
     S_BICG_CHECK,     // parts: |r|^2: iteration count, convergence and reliable-update flags
-    S_BICG_UPDATE,    // after a reliable update, parts: (rhat, r); parts2: |FP64 residual|^2: rho, convergence, restart
+    S_BICG_UPDATE,    // after a reliable update, parts: |FP64 residual|^2, (rhat, r): rho, convergence, restart
     S_CG_INIT,        // parts: |r|^2
     S_CG_ALPHA,       // parts: |Mhat p|^2
     S_CG_BETA,        // parts: |r|^2
