@@ -93,7 +93,7 @@ __device__ void bicg_init(const SSeg &a, const SParams &p, int rhs)
     s.done = b2 > 0 ? 0 : 1;
     s.fresh = 1;
     a.st[rhs] = s;
-    a.act[rhs] = b2 > 0 ? 1 : 0;
+    a.act[rhs] = b2 > 0 ? 3 : 0;  // 3: iterating, the iterate is still zero
     a.upd[rhs] = 0;
     a.restart[rhs] = 0;
 }
@@ -168,10 +168,10 @@ __device__ void bicg_update(const SSeg &a, const SParams &p, int rhs)
     sum_parts<3>(a.parts, rhs, a.nblk, d);
     if (threadIdx.x != 0) return;
     KState s = a.st[rhs];
-    int act = a.act[rhs], restart;
+    int act = a.act[rhs] != 0, restart;
     bicg_update_step(s, d + 1, d[0], s.maxiter, act, restart);
     if (p.mixed) s.fresh = 1;
-    a.act[rhs] = act;
+    a.act[rhs] = act && p.mixed ? 3 : act;
     a.restart[rhs] = restart;
     a.upd[rhs] = 0;
     a.st[rhs] = s;
@@ -277,7 +277,8 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
     using R = typename Fmt<S>::R;
     const int nb = (int)((a.Vh + BS - 1) / BS);
     const int rhs = item / nb, blk = item - rhs * nb;
-    if (masked_off(a.mask, rhs)) return;
+    const int flag = a.mask != nullptr ? __builtin_amdgcn_readfirstlane(a.mask[rhs]) : 1;
+    if (!flag) return;
     count_live(a.live, blk);
     const int64_t Vh = a.Vh;
     const int64_t cb = (int64_t)blk * BS + threadIdx.x;
@@ -297,14 +298,23 @@ __device__ __forceinline__ void vec_item(const VSeg &a, int item, double *red)
             const KState &k = a.st[rhs];
             const cx<R> alpha = ld_c<R>(k.alpha), omega = ld_c<R>(k.omega), beta = ld_c<R>(k.beta);
             cx<R> xv[12], sv[12], pv[12], tv[12], vv[12];
-            // an iterate that is still zero is neither cleared nor read
+            // An iterate that is still zero (the mask says so) is neither cleared nor
+            // read.  FP64, one wavefront per SIMD, asks for it after the other four
+            // fields: 24 right-hand sides at 8^3 x 16 27.1 us (34.0 asked for first,
+            // 29.2 without the branch; 288 at 16^3 x 32 the same either way); FP32 is
+            // 1% slower that way (12 right-hand sides at 12^3 x 24 34.6 and 33.8 us).
+            constexpr bool LATE = sizeof(R) == 8;
+            auto load_x = [&]() {
+                if (!(flag & 2)) load_spinor<S, true>(a.f[0], Vh, rhs, cb, xv);
+            };
 #pragma unroll
             for (int e = 0; e < 12; ++e) xv[e] = {R(0), R(0)};
-            if (!k.fresh) load_spinor<S, true>(a.f[0], Vh, rhs, cb, xv);
+            if constexpr (!LATE) load_x();
             load_spinor<S, true>(a.f[1], Vh, rhs, cb, sv);
             load_spinor<S, true>(a.f[2], Vh, rhs, cb, pv);
             load_spinor<S, true>(a.f[3], Vh, rhs, cb, tv);
             load_spinor<S, true>(a.f[4], Vh, rhs, cb, vv);
+            if constexpr (LATE) load_x();
 #pragma unroll
             for (int e = 0; e < 12; ++e) {
                 xv[e] = xv[e] + alpha * pv[e] + omega * sv[e];
