@@ -9,7 +9,7 @@
 // there, every thread the rest at its own sites, and barriers take the place
 // of launches.  The recursion, its scalars, the convergence and
 // reliable-update rules are those of the batched solver (bicg_* in
-// dl_blas.hip); only the order of the sums differs.
+// dl_krylov.hpp); only the order of the sums differs.
 #include <type_traits>
 
 #include "dl_dslash.hpp"
@@ -130,9 +130,11 @@ struct Own {
 // What bounds it: one CU's FP64 rate and the chain of its waits (at 384 sites
 // 52 us per iteration, 27 of them instructions being issued), whatever the
 // threads: with 512 the same within 5%, links loaded two or three hops ahead
-// no faster.  Measured on loops of 12 right-hand sides in FP64 (calls, with
-// their 300 us outside the solve): 4^4 2.00 -> 0.67 ms, 4^3 x 8 2.11 -> 1.03,
-// 4^2 x 6 x 8 2.18 -> 1.45; of 288: 2.97 -> 1.15, 4.14 -> 2.14, 4.86 -> 3.30.
+// no faster.  Measured on loops of 12 right-hand sides in FP64, whole calls
+// against the batched kernels' (which later lost 200 us outside the solve on
+// both sides): 4^4 2.00 -> 0.67 ms (0.45 now), 4^3 x 8 2.11 -> 1.03 (0.81),
+// 4^2 x 6 x 8 2.18 -> 1.45 (1.22); of 288: 2.97 -> 1.15 (0.93), 4.14 -> 2.14
+// (1.92), 4.86 -> 3.30 (3.20).
 // From 648 sites per parity on, the batched kernels' many CUs win.
 template <typename S, int NE, int K, int WAYS>
 __global__ __launch_bounds__(NT) void small_bicg_kernel(SmallArgs A)

@@ -230,22 +230,34 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
     float best_ms = 1e30f;
     std::vector<DslashCall> t = c;
     for (DslashCall &d : t) d.live_count = nullptr;
-    // in-place calls: candidates write a scratch field instead
-    std::vector<DevBuf> scratch;
+    // In-place calls are timed in place on a field that is put back afterwards.
+    // Timed with their output in a scratch field, the FP16 residual update of 416
+    // right-hand sides at 16^3 x 32 got two wavefronts per block in most runs, 4 ms
+    // per solve slower in place than the four it gets now.
+    std::vector<DevBuf> saved;
+    auto keep = [&](bool back) {
+        for (size_t k = 0; k < saved.size(); ++k) {
+            const DslashCall &d = t[k];
+            const size_t data = (size_t)d.nrhs * rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec));
+            const size_t nrm = d.prec == P16 ? (size_t)d.nrhs * (size_t)d.g.Vh * sizeof(float) : 0;
+            char *sv = saved[k].as<char>();
+            (void)hipMemcpyAsync(back ? d.out.d : sv, back ? sv : d.out.d, data, hipMemcpyDeviceToDevice, s);
+            if (nrm)
+                (void)hipMemcpyAsync(back ? (void *)d.out.nrm : sv + data, back ? sv + data : (char *)d.out.nrm, nrm,
+                                     hipMemcpyDeviceToDevice, s);
+        }
+    };
     if (in_place(c)) {
         try {
-            for (DslashCall &d : t) {
-                const size_t data = (size_t)d.nrhs * rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec));
-                const size_t nrm = d.prec == P16 ? (size_t)d.nrhs * (size_t)d.g.Vh * sizeof(float) : 0;
-                scratch.emplace_back(data + nrm);
-                d.out.d = scratch.back().p;
-                d.out.nrm = nrm ? reinterpret_cast<float *>(static_cast<char *>(scratch.back().p) + data) : nullptr;
-            }
+            for (DslashCall &d : t)
+                saved.emplace_back((size_t)d.nrhs * (rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec)) +
+                                                     (d.prec == P16 ? (size_t)d.g.Vh * sizeof(float) : 0)));
         } catch (...) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return dflt;
         }
+        keep(false);
     }
     std::vector<TuneChoice> cands{dflt};
     for (const TuneChoice &cand : candidates(c[0].prec, c[0].recon))
@@ -274,6 +286,7 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
             best = cand;
         }
     }
+    keep(true);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     g_cache[k] = best;
