@@ -1827,6 +1827,15 @@ std::vector<double> adjoint_matrices(const std::vector<double> &gtab, const int3
     return A;
 }
 
+// A gradient's forward and adjoint systems are solved as one batch up to this
+// many wavefronts (right-hand sides times 64-site blocks) of each: their
+// launches leave the chip idle.  FP64 calls with the kappa derivative, one
+// after the other and together: 768 wavefronts (12 right-hand sides at
+// 8^3 x 16) 5.5 and 4.8 ms, 1536 8.42 and 7.38, 3840 15.6 and 14.3, 7776
+// (24 at 12^3 x 24) 28.7 and 27.2, 12288 (12 at 16^3 x 32) 42.2 and 41.6 for
+// twice the workspace.
+constexpr int64_t PAIR_WAVES = 8192;
+
 // The loop estimator and its derivatives over a batch loop of whole noises.
 //   MODE_LOOPS:  out[n][g][t] = sum_d eta^+ P_t Gamma s, s = M^-1 eta
 //   MODE_DKAPPA: out[n][g][t] = sum_d eta^+ P_t Gamma u, u = M^-1 D M^-1 eta
@@ -1909,9 +1918,14 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                 k_source(prec, be, bo, ss, c.g, n, c.s);
             }
         };
-        SolveWork w;
+        SolveWork w, wk;
+        // one per solve, of the right-hand sides that it had (both solves' where they are one)
         std::vector<std::unique_ptr<SolveReport>> report(nsolve);
         int sol_prec = P64;
+        // The adjoint system does not need the forward solution: where the launches
+        // of one of them leave the chip idle both are solved as one batch.
+        const bool pair = mode == MODE_GRAD && (int64_t)n * ((Vh + 63) / 64) <= PAIR_WAVES &&
+                          2 * (int64_t)n <= 65535 && 2 * per * (size_t)n <= workspace_limit();
         if (cg) {
             w.alloc_cgnr(prm.prec, n, Vh);
             make_source(prm.prec, w.be.view(), w.bo.view());
@@ -1919,8 +1933,9 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
             sol_prec = prm.prec;
             report[0].reset(new SolveReport(c, kappa, w, true, false));
         } else {
-            w.alloc_bicg(prm.prec, n, Vh);
+            w.alloc_bicg(prm.prec, pair ? 2 * n : n, Vh);
             make_source(P64, w.be.view(), w.bo.view());
+            if (pair) k_adjoint_source(w.be.view_rhs(n), w.bo.view_rhs(n), ss, c.g, n, dA.as<double>(), c.s);
             bicgstab_batch(c, kappa, prm, w);
             report[0].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
             if (mode == MODE_DKAPPA) {
@@ -1935,35 +1950,44 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
                 report[1].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
             } else if (mode == MODE_GRAD) {
                 HalfField se, so;
-                se.alloc(P64, n, Vh);
-                so.alloc(P64, n, Vh);
-                k_copy(P64, se.view(), P64, w.x64.view(), Vh, n, nullptr, c.s);
-                k_copy(P64, so.view(), P64, w.xo.view(), Vh, n, nullptr, c.s);
+                Field fe = w.x64.view(), fo = w.xo.view();
+                if (pair) {
+                    if (dout_host) wk.alloc_bicg(prm.prec, n, Vh);
+                } else {
+                    se.alloc(P64, n, Vh);
+                    so.alloc(P64, n, Vh);
+                    k_copy(P64, se.view(), P64, fe, Vh, n, nullptr, c.s);
+                    k_copy(P64, so.view(), P64, fo, Vh, n, nullptr, c.s);
+                    fe = se.view();
+                    fo = so.view();
+                }
+                SolveWork &w2 = pair ? wk : w;
                 if (out_host) {
-                    k_trace(P64, se.view(), so.view(), ss, c.g, n, dC.as<double>(), c.s);
+                    k_trace(P64, fe, fo, ss, c.g, n, dC.as<double>(), c.s);
                     k_gamma_contract(dC.as<double>(), nn, ncls, T, gset,
                                      dloops.as<double>() + (r0 / ncls) * n_gamma * T * 2, c.s);
                 }
                 if (dout_host) {
                     // kappa derivative: u = M^-1 D s
-                    launch_dslash(dcall(c, P64, 0, false, EPI_PLAIN, so.view(), w.be.view(), NOF, NOF, 1.0, n,
+                    launch_dslash(dcall(c, P64, 0, false, EPI_PLAIN, fo, w2.be.view(), NOF, NOF, 1.0, n,
                                         nullptr, nullptr),
                                   c.s);
-                    launch_dslash(dcall(c, P64, 1, false, EPI_PLAIN, se.view(), w.bo.view(), NOF, NOF, 1.0, n,
+                    launch_dslash(dcall(c, P64, 1, false, EPI_PLAIN, fe, w2.bo.view(), NOF, NOF, 1.0, n,
                                         nullptr, nullptr),
                                   c.s);
-                    bicgstab_batch(c, kappa, prm, w);
-                    report[2].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
-                    k_trace(P64, w.x64.view(), w.xo.view(), ss, c.g, n, dC.as<double>(), c.s);
+                    bicgstab_batch(c, kappa, prm, w2);
+                    report[2].reset(new SolveReport(c, kappa, w2, false, stats != nullptr));
+                    k_trace(P64, w2.x64.view(), w2.xo.view(), ss, c.g, n, dC.as<double>(), c.s);
                     k_gamma_contract(dC.as<double>(), nn, ncls, T, gset,
                                      ddk.as<double>() + (r0 / ncls) * n_gamma * T * 2, c.s);
                 }
-                const double *Ab = dA.as<double>();
-                k_adjoint_source(w.be.view(), w.bo.view(), ss, c.g, n, Ab, c.s);
-                bicgstab_batch(c, kappa, prm, w);
-                report[1].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
-                k_link_grad(se.view(), so.view(), w.x64.view(), w.xo.view(), c.g, n, kappa, dgrad.as<double>(),
-                            c.s);
+                if (!pair) {
+                    k_adjoint_source(w.be.view(), w.bo.view(), ss, c.g, n, dA.as<double>(), c.s);
+                    bicgstab_batch(c, kappa, prm, w);
+                    report[1].reset(new SolveReport(c, kappa, w, false, stats != nullptr));
+                }
+                k_link_grad(fe, fo, w.x64.view_rhs(pair ? n : 0), w.xo.view_rhs(pair ? n : 0), c.g, n, kappa,
+                            dgrad.as<double>(), c.s);
             }
         }
         if (mode != MODE_GRAD) {
@@ -1985,14 +2009,15 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
         DL_HIP(hipStreamSynchronize(c.s));
         // each solve's share of the round's time: the solves of one round are alike
         const double secs = sw.lap() / ((double)nsolve * n);
-        std::vector<dl_solve_stats> st(n);
-        for (int k = 0; k < nsolve; ++k) {
-            report[k]->fill(st.data(), sw, secs);
+        std::vector<dl_solve_stats> st((size_t)nsolve * n);
+        for (int k = 0; k < nsolve; ++k)
+            if (report[k]) report[k]->fill(st.data() + (size_t)k * n, sw, secs);
+        for (int k = 0; k < nsolve; ++k)
             for (int i = 0; i < n; ++i) {
-                if (stats) stats[(int64_t)k * total + r0 + i] = st[i];
-                if (st[i].status != DL_OK && worst == DL_OK) worst = st[i].status;
+                const dl_solve_stats &one = st[(size_t)k * n + i];
+                if (stats) stats[(int64_t)k * total + r0 + i] = one;
+                if (one.status != DL_OK && worst == DL_OK) worst = one.status;
             }
-        }
     }
     loops_pin.wait();
     if (out_host && pinned) std::memcpy(out_host, loops_pin.as<char>(), dloops.bytes);

@@ -179,3 +179,28 @@ def test_hops_dealt_out_over_workgroups(dl, dev, monkeypatch, dims, nrhs, cfg):
     for r in {0, nrhs // 2, nrhs - 1}:
         assert st[r][0] == dl.DL_OK
         assert oracle_residual(U, x[r], psi[r], dims, kappa) <= 1.5e-10
+
+
+# one and two rounds of noises; the forward and adjoint systems as one batch (the default) and, where the workspace
+# holds no more than one noise, one after the other.  Both solve to 1e-10 on operators of condition number below 30.
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 6, 10)])
+@pytest.mark.parametrize("prec,with_dkappa", [(0, True), (0, False), (1, True)])
+def test_gradient_solves_together_and_apart(dl, dev, monkeypatch, dims, prec, with_dkappa):
+    U = synth.gauge_field(dims, 0.35, seed=931)
+    G = dl.Gauge(dl.Lattice(dims, 1), U, precs=(dl.DL_F64, dl.DL_F32))
+    src = dl.z2_sources(932, 2, scheme=dl.DL_DIL_SPIN_COLOUR)
+    rng = np.random.default_rng(933)
+    w = rng.standard_normal((2, 2, dims[3])) + 1j * rng.standard_normal((2, 2, dims[3]))
+    params = dl.solve_params(prec=prec, tol=1e-10, maxiter=2000)
+    one = dl.loops_link_grad(G, 0.13, src, [0, 15], w, params, with_dkappa=with_dkappa)
+    grad = np.array(one[0])
+    monkeypatch.setenv("DL_WORKSPACE_GB", "0.001")
+    two = dl.loops_link_grad(G, 0.13, src, [0, 15], w, params, with_dkappa=with_dkappa)
+    assert np.linalg.norm(grad - np.array(two[0])) <= 1e-8 * np.linalg.norm(grad)
+    assert np.linalg.norm(one[1] - two[1]) <= 1e-8 * np.linalg.norm(one[1])
+    if with_dkappa:
+        assert np.linalg.norm(one[2] - two[2]) <= 1e-8 * np.linalg.norm(one[2])
+    nsolve = 3 if with_dkappa else 2
+    assert len(one[4]) >= nsolve * 24
+    for a, b in zip(one[4][:nsolve * 24], two[4][:nsolve * 24]):
+        assert a[0] == b[0] == dl.DL_OK and abs(a[1] - b[1]) <= 1 and a[3] <= 1e-10 and b[3] <= 1e-10
