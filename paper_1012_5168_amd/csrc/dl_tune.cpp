@@ -224,16 +224,16 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
     // (one launch of a 288-right-hand-side hop takes a few ms and varies by a
     // few percent from launch to launch); a candidate's time is the better of
     // two samples.  The default goes first and a later candidate must beat
-    // the best so far by 3%: near-ties keep the earlier choice, so the result
-    // does not wander between equivalent configurations.
+    // the best so far by 1%, one of the other kernel by 3%: near-ties keep the
+    // earlier choice, so the result does not wander between equivalent
+    // configurations.  (With 3% for all, the FP16 residual update of 416
+    // right-hand sides at 16^3 x 32 kept two wavefronts per block at 1407 us
+    // against four at 1370, which are 160 us apart in the solver.)
     TuneChoice best = dflt;
     float best_ms = 1e30f;
     std::vector<DslashCall> t = c;
     for (DslashCall &d : t) d.live_count = nullptr;
     // In-place calls are timed in place on a field that is put back afterwards.
-    // Timed with their output in a scratch field, the FP16 residual update of 416
-    // right-hand sides at 16^3 x 32 got two wavefronts per block in most runs, 4 ms
-    // per solve slower in place than the four it gets now.
     std::vector<DevBuf> saved;
     auto keep = [&](bool back) {
         for (size_t k = 0; k < saved.size(); ++k) {
@@ -281,7 +281,8 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
             ms = sample(cand, reps);
         }
         const float per = std::min(ms, sample(cand, reps)) / reps;
-        if (hipGetLastError() == hipSuccess && per < 0.97f * best_ms) {
+        const float margin = cand.kind == best.kind ? 0.99f : 0.97f;
+        if (hipGetLastError() == hipSuccess && per < margin * best_ms) {
             best_ms = per;
             best = cand;
         }
