@@ -1923,9 +1923,24 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
         std::vector<std::unique_ptr<SolveReport>> report(nsolve);
         int sol_prec = P64;
         // The adjoint system does not need the forward solution: where the launches
-        // of one of them leave the chip idle both are solved as one batch.
-        const bool pair = mode == MODE_GRAD && (int64_t)n * ((Vh + 63) / 64) <= PAIR_WAVES &&
-                          2 * (int64_t)n <= 65535 && 2 * per * (size_t)n <= workspace_limit();
+        // of one of them leave the chip idle both are solved as one batch, in a
+        // workspace of both.  The kappa solve does need it, and takes a third while
+        // the pair's is held.  Where the limit or the device has no room for them,
+        // the systems are solved one after the other in one workspace.
+        const size_t together = (dout_host ? 3 : 2) * SolveWork::bytes_bicg(prm.prec, Vh) + (size_t)T * 32 * 8;
+        bool pair = mode == MODE_GRAD && (int64_t)n * ((Vh + 63) / 64) <= PAIR_WAVES && 2 * (int64_t)n <= 65535 &&
+                    together * (size_t)n <= workspace_limit();
+        if (pair) {
+            try {
+                w.alloc_bicg(prm.prec, 2 * n, Vh);
+                if (dout_host) wk.alloc_bicg(prm.prec, n, Vh);
+            } catch (const Error &e) {
+                if (e.code != DL_ENOMEM) throw;
+                w = SolveWork();
+                wk = SolveWork();
+                pair = false;
+            }
+        }
         if (cg) {
             w.alloc_cgnr(prm.prec, n, Vh);
             make_source(prm.prec, w.be.view(), w.bo.view());
@@ -1933,7 +1948,7 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
             sol_prec = prm.prec;
             report[0].reset(new SolveReport(c, kappa, w, true, false));
         } else {
-            w.alloc_bicg(prm.prec, pair ? 2 * n : n, Vh);
+            if (!pair) w.alloc_bicg(prm.prec, n, Vh);
             make_source(P64, w.be.view(), w.bo.view());
             if (pair) k_adjoint_source(w.be.view_rhs(n), w.bo.view_rhs(n), ss, c.g, n, dA.as<double>(), c.s);
             bicgstab_batch(c, kappa, prm, w);
@@ -1951,9 +1966,7 @@ int loops_run(dl_gauge G, double kappa, const dl_sources *src, const dl_solve_pa
             } else if (mode == MODE_GRAD) {
                 HalfField se, so;
                 Field fe = w.x64.view(), fo = w.xo.view();
-                if (pair) {
-                    if (dout_host) wk.alloc_bicg(prm.prec, n, Vh);
-                } else {
+                if (!pair) {
                     se.alloc(P64, n, Vh);
                     so.alloc(P64, n, Vh);
                     k_copy(P64, se.view(), P64, fe, Vh, n, nullptr, c.s);

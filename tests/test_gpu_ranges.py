@@ -204,3 +204,53 @@ def test_gradient_solves_together_and_apart(dl, dev, monkeypatch, dims, prec, wi
     assert len(one[4]) >= nsolve * 24
     for a, b in zip(one[4][:nsolve * 24], two[4][:nsolve * 24]):
         assert a[0] == b[0] == dl.DL_OK and abs(a[1] - b[1]) <= 1 and a[3] <= 1e-10 and b[3] <= 1e-10
+
+
+def _gradient_call(dl, dims, nrhs, kappa=0.13):
+    U = synth.gauge_field(dims, 0.35, seed=961)
+    G = dl.Gauge(dl.Lattice(dims, 1), U)
+    src = dl.z2_sources(962, nrhs)
+    rng = np.random.default_rng(963)
+    w = rng.standard_normal((nrhs, 2, dims[3])) + 1j * rng.standard_normal((nrhs, 2, dims[3]))
+    params = dl.solve_params(tol=1e-10, maxiter=2000)
+    return lambda: dl.loops_link_grad(G, kappa, src, [0, 15], w, params, with_dkappa=True)
+
+
+def _same_gradient(one, two):
+    return all(np.linalg.norm(np.array(a) - np.array(b)) <= 1e-8 * np.linalg.norm(np.array(a))
+               for a, b in zip(one[:3], two[:3]))
+
+
+# half fields of 4096 sites in FP64: 9.4 MB of 12 right-hand sides; a solve holds at least 12 of them.  The limits hold
+# one solve (0.15 GB), two but not the third that the kappa derivative needs beside a pair (0.3), and all three (0.5)
+@pytest.mark.parametrize("limit", [0.15, 0.3, 0.5])
+def test_gradient_keeps_the_workspace_limit(dl, dev, monkeypatch, limit):
+    run = _gradient_call(dl, (8, 8, 8, 16), 12)
+    ref = run()
+    monkeypatch.setenv("DL_WORKSPACE_GB", str(limit))
+    dl.dl_cache_release()
+    out = run()
+    # every buffer of the call is in the cache now; beside the workspace the gradient [4][V][9] complex128, the
+    # adjoint sources' matrices and the loops
+    held = dl.dl_cache_bytes() - 4 * 8192 * 9 * 16 - (1 << 20)
+    assert 0.1e9 < held <= limit * 1e9, held
+    assert _same_gradient(ref, out)
+
+
+def test_gradient_on_a_nearly_full_device(dl, dev):
+    """Twice a solve's workspace is left on the device: the forward and adjoint systems as one batch with the kappa
+    solve beside them (three of them) do not fit, one after the other they do."""
+    nrhs, dims = 8, (16, 16, 16, 32)
+    run = _gradient_call(dl, dims, nrhs)
+    ref = run()
+    dl.dl_cache_release()
+    torch.cuda.empty_cache()
+    solve = 13 * nrhs * (int(np.prod(dims)) // 2) * 192
+    hog = torch.empty(torch.cuda.mem_get_info()[0] - 2 * solve, dtype=torch.uint8, device=dev)
+    try:
+        out = run()
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+        dl.dl_cache_release()
+    assert _same_gradient(ref, out)
