@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <complex>
@@ -59,28 +60,42 @@ namespace dl {
 // stream is known the release synchronises the device instead, as hipFree
 // would; where the call's stream has run dry by then (most calls end with a
 // synchronisation) no event is needed.  The cached bytes are capped
-// (DL_CACHE_GB, default 64 GB, or dl_cache_set_limit; 0 turns the cache off):
-// the blocks released longest ago make room, so that a process that has moved
-// on to other shapes still has its present ones cached (turned away at a full
-// cache instead, 96 fields at 16^3 x 32 cost 65 ms of mapping memory per
-// dl_apply of 3.5 ms); dl_cache_release frees all of it; an allocation that
-// fails releases the cache and tries again.
+// (DL_CACHE_GB, default 64 GB, or dl_cache_set_limit; 0 turns the cache off).
+// A full cache turns a block away until two earlier calls have had one of its
+// size turned away; then the blocks that no call has used since the first of
+// these make room, the longest unused first.  A process that has moved on to
+// other shapes has them cached after two calls (turned away for good, 96 fields
+// at 16^3 x 32 cost 65 ms of mapping memory per dl_apply of 3.5 ms), and of
+// shapes that take turns and do not all fit, the first stay (evicted on each
+// release instead, two that alternate mapped both of their workspaces on every
+// call).  dl_cache_release frees all of it; an allocation that fails releases
+// the cache and tries again.  Blocks are freed (hipFree waits for the device)
+// with g_free_mu held, which only callers that free take, and never with
+// g_cache_mu; it is taken before a block leaves the cache to be freed, so that a
+// caller out of memory waits for the blocks that others are freeing.
 namespace {
 struct CacheEntry {
     void *p;
     hipEvent_t ready;  // recorded after the block's last use (null: its stream was idle)
-    uint64_t stamp;    // order of release
+    uint64_t call;     // the call that released it
 };
-std::mutex g_cache_mu;
-std::multimap<std::pair<int, size_t>, CacheEntry> g_cache_free;
+struct TurnedAway {
+    uint64_t now = 0, last = 0, first = 0;  // the latest calls that had a block of one size turned away
+};
+using CacheKey = std::pair<int, size_t>;  // device, bytes
+std::mutex g_free_mu, g_cache_mu;         // in this order
+std::multimap<CacheKey, CacheEntry> g_cache_free;
+std::map<CacheKey, TurnedAway> g_cache_turned;
+constexpr size_t TURNED_MAX = 1024;  // sizes remembered
 size_t g_cache_bytes = 0;
-uint64_t g_cache_stamp = 0;
+std::atomic<uint64_t> g_calls{0};
 bool g_cache_limit_set = false;
 size_t g_cache_limit = 0;
 
 // the stream of the entry point running on this thread (StreamScope)
 thread_local bool t_stream_known = false;
 thread_local hipStream_t t_stream = nullptr;
+thread_local uint64_t t_call = 0;  // its number
 
 size_t cache_limit_locked()
 {
@@ -100,26 +115,79 @@ int current_device()
     return d;
 }
 
-void free_entry(const CacheEntry &c)
+using CacheIter = std::multimap<CacheKey, CacheEntry>::iterator;
+
+// the cached blocks, the longest unused first
+std::vector<CacheIter> cache_by_age_locked()
 {
-    if (c.ready) {
-        (void)hipEventSynchronize(c.ready);
-        (void)hipEventDestroy(c.ready);
-    }
-    (void)hipFree(c.p);
+    std::vector<CacheIter> v;
+    for (auto it = g_cache_free.begin(); it != g_cache_free.end(); ++it) v.push_back(it);
+    std::stable_sort(v.begin(), v.end(), [](CacheIter x, CacheIter y) { return x->second.call < y->second.call; });
+    return v;
 }
 
-// free cached blocks, the longest unused first, until at most `keep` bytes remain
-void cache_trim_locked(size_t keep)
+// Takes blocks out of the cache, the longest unused first and only those unused
+// since before call `since`, until at most `keep` bytes remain; none, and false,
+// where these do not make it so.
+bool cache_take_locked(size_t keep, uint64_t since, std::vector<CacheEntry> &out)
 {
-    while (g_cache_bytes > keep && !g_cache_free.empty()) {
-        auto it = std::min_element(g_cache_free.begin(), g_cache_free.end(), [](const auto &x, const auto &y) {
-            return x.second.stamp < y.second.stamp;
-        });
-        free_entry(it->second);
-        g_cache_bytes -= it->first.second;
+    size_t left = g_cache_bytes;
+    std::vector<CacheIter> go;
+    if (left > keep)
+        for (CacheIter it : cache_by_age_locked()) {
+            if (left <= keep || it->second.call >= since) break;
+            left -= it->first.second;
+            go.push_back(it);
+        }
+    if (left > keep) return false;
+    out.reserve(out.size() + go.size());
+    for (CacheIter it : go) {
+        out.push_back(it->second);
         g_cache_free.erase(it);
     }
+    g_cache_bytes = left;
+    return true;
+}
+
+void free_entries(const std::vector<CacheEntry> &v)
+{
+    for (const CacheEntry &c : v) {
+        if (c.ready) {
+            (void)hipEventSynchronize(c.ready);
+            (void)hipEventDestroy(c.ready);
+        }
+        (void)hipFree(c.p);
+    }
+}
+
+// free cached blocks until at most `keep` bytes remain
+void cache_trim(size_t keep)
+{
+    std::lock_guard<std::mutex> freeing(g_free_mu);
+    std::vector<CacheEntry> out;
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        cache_take_locked(keep, UINT64_MAX, out);
+    }
+    free_entries(out);
+}
+
+// Puts a block into the cache if there is room, or if room may be made (see
+// above; `out` then holds the blocks to free, or is null where none may go).
+bool cache_put_locked(const CacheKey &key, const CacheEntry &c, std::vector<CacheEntry> *out)
+{
+    const size_t limit = cache_limit_locked();
+    if (key.second > limit) return false;
+    if (g_cache_bytes + key.second > limit) {
+        if (!out) return false;
+        if (g_cache_turned.size() >= TURNED_MAX) g_cache_turned.clear();
+        TurnedAway &t = g_cache_turned[key];
+        if (t.now != c.call) t = TurnedAway{c.call, t.now, t.last};
+        if (!cache_take_locked(limit - key.second, t.first, *out)) return false;
+    }
+    g_cache_free.insert({key, c});
+    g_cache_bytes += key.second;
+    return true;
 }
 }  // namespace
 
@@ -133,6 +201,7 @@ bool no_alloc_active() { return t_no_alloc; }
 
 StreamScope::StreamScope(void *stream) : prev_known(t_stream_known), prev(t_stream)
 {
+    if (!prev_known) t_call = ++g_calls;
     t_stream_known = true;
     t_stream = static_cast<hipStream_t>(stream);
 }
@@ -177,10 +246,7 @@ void DevBuf::alloc(size_t n)
     hipError_t e = hipMalloc(&p, n);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
         (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lk(g_cache_mu);
-            cache_trim_locked(0);
-        }
+        cache_trim(0);
         e = hipMalloc(&p, n);
     }
     if (e != hipSuccess) {
@@ -220,14 +286,21 @@ void DevBuf::release() noexcept
         if (!idle && !(t_stream_known && capturing(t_stream))) idle = hipDeviceSynchronize() == hipSuccess;
         if (idle) {
             try {
-                std::lock_guard<std::mutex> lk(g_cache_mu);
-                const size_t now = cache_limit_locked();
-                if (cap <= now) {
-                    cache_trim_locked(now - cap);
-                    c.stamp = ++g_cache_stamp;
-                    g_cache_free.insert({{current_device(), cap}, c});
-                    g_cache_bytes += cap;
-                    cached = true;
+                const CacheKey key{current_device(), cap};
+                c.call = t_stream_known ? t_call : ++g_calls;
+                {
+                    std::lock_guard<std::mutex> lk(g_cache_mu);
+                    cached = cache_put_locked(key, c, nullptr);
+                }
+                if (!cached) {
+                    std::lock_guard<std::mutex> freeing(g_free_mu);
+                    std::vector<CacheEntry> out;
+                    try {
+                        std::lock_guard<std::mutex> lk(g_cache_mu);
+                        cached = cache_put_locked(key, c, &out);
+                    } catch (...) {
+                    }
+                    free_entries(out);
                 }
             } catch (...) {
                 cached = false;
@@ -2404,10 +2477,7 @@ extern "C" int dl_eta_prime_fit(const double *d, const double *c_pi, int32_t ncf
 extern "C" int dl_cache_release(void)
 {
     return guarded([&]() {
-        {
-            std::lock_guard<std::mutex> lk(g_cache_mu);
-            cache_trim_locked(0);
-        }
+        cache_trim(0);
         pin_release_all();
         return DL_OK;
     });
@@ -2416,10 +2486,12 @@ extern "C" int dl_cache_release(void)
 extern "C" int dl_cache_set_limit(uint64_t bytes)
 {
     return guarded([&]() {
-        std::lock_guard<std::mutex> lk(g_cache_mu);
-        g_cache_limit = (size_t)bytes;
-        g_cache_limit_set = true;
-        cache_trim_locked(g_cache_limit);
+        {
+            std::lock_guard<std::mutex> lk(g_cache_mu);
+            g_cache_limit = (size_t)bytes;
+            g_cache_limit_set = true;
+        }
+        cache_trim((size_t)bytes);
         return DL_OK;
     });
 }

@@ -1,6 +1,9 @@
 """The device memory cache: calls served from cached blocks (including a block
 larger than the request) give the same results, bit for bit, as calls that
 allocate afresh, and dl_cache_release empties the cache between calls."""
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -72,3 +75,64 @@ def test_full_cache_makes_room_for_the_shapes_in_use(dl, dev):
         dl.dl_cache_set_limit(64 << 30)
         dl.dl_cache_release()
     assert dl.dl_cache_bytes() == 0
+
+
+def test_shapes_that_take_turns_at_a_full_cache(dl, dev):
+    """A cap that holds one shape's workspaces but not two: while the shapes take turns the first one's fields stay
+    cached (a small block that the second borrows may find its place taken); once only the second is called, its
+    fields are cached too."""
+    dims = (6, 4, 6, 10)
+    field = int(np.prod(dims)) // 2 * 96  # the smallest field of a right-hand side: FP32
+    U = synth.gauge_field(dims, 0.5, seed=621)
+    G = dl.Gauge(dl.Lattice(dims, 1), U, precs=(dl.DL_F64, dl.DL_F32))
+    prm = dl.solve_params(prec=dl.DL_F32, tol=1e-10, maxiter=2000)
+    big, small = dl.z2_sources(6210, 8), dl.z2_sources(6210, 3)
+
+    def run(src):
+        return dl.loops(G, 0.124, src, [0, 15], prm)[0]
+
+    dl.dl_cache_release()
+    small_ref = run(small)
+    dl.dl_cache_release()
+    ref = run(big)
+    limit = dl.dl_cache_bytes()
+    try:
+        dl.dl_cache_set_limit(limit)
+        for _ in range(4):
+            assert np.array_equal(run(small), small_ref) and 0 <= limit - dl.dl_cache_bytes() < 8 * field
+            assert np.array_equal(run(big), ref) and 0 <= limit - dl.dl_cache_bytes() < 8 * field
+        full = dl.dl_cache_bytes()
+        for _ in range(3):
+            assert np.array_equal(run(small), small_ref) and dl.dl_cache_bytes() <= limit
+        held = dl.dl_cache_bytes()
+        assert abs(held - full) > 3 * field  # fields of 3 right-hand sides in the place of fields of 8
+        assert np.array_equal(run(small), small_ref) and dl.dl_cache_bytes() == held
+    finally:
+        dl.dl_cache_set_limit(64 << 30)
+        dl.dl_cache_release()
+
+
+def test_freeing_blocks_does_not_hold_up_other_threads(dl, dev):
+    """Freeing a block waits for the device; meanwhile another thread's use of the cache does not."""
+    dims = (6, 4, 6, 10)
+    G = dl.Gauge(dl.Lattice(dims, 1), synth.gauge_field(dims, 0.5, seed=631))
+    prm = dl.solve_params(tol=1e-10, maxiter=2000)
+    dl.loops(G, 0.124, dl.z2_sources(6310, 2), [0, 15], prm)
+    assert dl.dl_cache_bytes() > 0
+    a = torch.randn((8192, 8192), device=dev, dtype=torch.bfloat16)
+    torch.mm(a, a)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for _ in range(1000):  # about a second
+            torch.mm(a, a)
+    releasing = threading.Thread(target=dl.dl_cache_release)
+    releasing.start()
+    time.sleep(0.1)
+    waits = releasing.is_alive()
+    t0 = time.perf_counter()
+    dl.dl_cache_bytes()
+    took = time.perf_counter() - t0
+    releasing.join()
+    torch.cuda.synchronize()
+    assert took < 0.1 or not waits, took
