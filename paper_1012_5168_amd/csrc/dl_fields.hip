@@ -713,10 +713,35 @@ void k_smear(const void *links, int recon, Field ine, Field ino, Field oute, Fie
     }
 }
 
-// Whether smear_chip_kernel takes a field: up to two sites of each parity per
-// thread (three would not leave the registers of 1024 threads room for a step),
-// 96 KiB of LDS, and a grid of (timeslice, field, spin) problems below 2^31.
-bool smear_chip_fits(const Geom &g, int nrhs) { return g.sT <= 2048 && 4LL * g.T * nrhs < (1LL << 31); }
+// Workgroup of smear_chip_kernel: one site of each parity per thread up to 512,
+// two up to 1024 and four up to 2048 (1024 threads of two sites have no
+// registers to load a link ahead).
+static int smear_chip_threads(int H) { return H <= 64 ? 64 : H <= 128 ? 128 : H <= 256 ? 256 : 512; }
+
+// Whether smear_chip_kernel takes the fields, a (timeslice, field, spin) problem
+// per workgroup, or smear_kernel step by step.  Up to 2048 sites per parity and
+// timeslice (96 KiB of LDS, four sites of each parity per thread), and where it
+// is faster.  Measured for 1 to 50 steps on 1 to 400 fields, on chip against
+// step by step, whole calls:
+// * 32 to 1024 sites: always (50 steps on one field 145 against 600-800 us, ten
+//   on 400 fields 0.83-0.89 of the time at 32 sites, 0.5 from 108 on).
+// * Below 32 sites most lanes of the workgroup idle, and many problems take
+//   longer: ten steps on 3200 problems 114 against 193 us at 4 sites, on 6144 170
+//   against 135-156 at 4 and 8 sites and 178 against 177 at 16, on 25600 600 and
+//   160.
+// * Above 1024 sites a step takes a CU 18 us however few the problems are, a
+//   launch per step 13-15 us until it fills the chip: 50 steps on 32 problems of
+//   1536 sites 912 against 664 us, on 128 of 1152 (147 thousand sites) 914 and
+//   872, on 96 of 1792 (172 thousand) 996 and 1051, on 256 of 2048 1226 and 1998.
+bool smear_chip_fits(const Geom &g, int nrhs)
+{
+    const int64_t problems = 4LL * g.T * nrhs;
+    if (g.sT > 2048) return false;
+    if (problems * smear_chip_threads(g.sT) >= (1LL << 32)) return false;  // threads of one launch
+    if (g.sT < 32) return problems <= 4096;
+    if (g.sT > 1024) return problems * g.sT > 160000;
+    return true;
+}
 
 template <int NE, bool CANON>
 static void smear_chip_go(const void *links, const SmearIO &io, const Geom &g, int nrhs, double alpha, int iters,
@@ -725,23 +750,23 @@ static void smear_chip_go(const void *links, const SmearIO &io, const Geom &g, i
     const double norm = 1.0 / (1.0 + 6.0 * alpha);
     const dim3 grid(4u * g.T * nrhs);
     const size_t lds = (size_t)3 * g.sT * 16;
-    auto go = [&](auto kernel, int nt) {
+    auto go = [&](auto kernel) {
         DL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    3 * 2048 * 16));
-        hipLaunchKernelGGL(kernel, grid, dim3(nt), lds, s, links, io, g, alpha, norm, iters, nrhs);
+        hipLaunchKernelGGL(kernel, grid, dim3(smear_chip_threads(g.sT)), lds, s, links, io, g, alpha, norm, iters, nrhs);
     };
     if (g.sT <= 64)
-        go(smear_chip_kernel<NE, 64, 1, CANON>, 64);
+        go(smear_chip_kernel<NE, 64, 1, CANON>);
     else if (g.sT <= 128)
-        go(smear_chip_kernel<NE, 128, 1, CANON>, 128);
+        go(smear_chip_kernel<NE, 128, 1, CANON>);
     else if (g.sT <= 256)
-        go(smear_chip_kernel<NE, 256, 1, CANON>, 256);
+        go(smear_chip_kernel<NE, 256, 1, CANON>);
     else if (g.sT <= 512)
-        go(smear_chip_kernel<NE, 512, 1, CANON>, 512);
+        go(smear_chip_kernel<NE, 512, 1, CANON>);
     else if (g.sT <= 1024)
-        go(smear_chip_kernel<NE, 512, 2, CANON>, 512);
+        go(smear_chip_kernel<NE, 512, 2, CANON>);
     else
-        go(smear_chip_kernel<NE, 512, 4, CANON>, 512);
+        go(smear_chip_kernel<NE, 512, 4, CANON>);
 }
 
 void k_smear_chip(const void *links, int recon, const SmearIO &io, bool canon, const Geom &g, int nrhs, double alpha,

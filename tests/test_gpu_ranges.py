@@ -254,3 +254,46 @@ def test_gradient_on_a_nearly_full_device(dl, dev):
         torch.cuda.empty_cache()
         dl.dl_cache_release()
     assert _same_gradient(ref, out)
+
+
+# both sides of the rule that sends smearing on chip or step by step: few and many (timeslice, field, spin) problems of
+# 4 and 16 sites per parity (64 to 65 fields of 16 timeslices), and of 1152, 1536 and 2048 (the last two sizes with
+# four sites of each parity per thread, the first ragged)
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 16), 64), ((2, 2, 2, 16), 65), ((4, 4, 2, 16), 64), ((4, 4, 2, 16), 65),
+                                       ((16, 12, 12, 2), 17), ((16, 12, 12, 2), 18), ((16, 16, 12, 2), 14),
+                                       ((16, 16, 16, 2), 10)])
+def test_smearing_on_chip_and_step_by_step(dl, dev, dims, nrhs, recon):
+    U = synth.gauge_field(dims, 0.6, seed=971)
+    G = dl.Gauge(dl.Lattice(dims, 1), U, recon=recon)
+    psi = synth.random_spinor(dims, nrhs, seed=972)
+    out = from_dev(dl.smear(G, 0.5, 3, to_dev(psi, dev)))
+    for r in (0, nrhs // 2, nrhs - 1):
+        ref = oracle.smear(U, psi[r], dims, 0.5, 3)
+        assert np.max(np.abs(out[r] - ref)) <= 1e-13 * np.max(np.abs(ref)), r
+
+
+def test_smearing_of_the_most_fields(dl, dev):
+    """65535 fields of 258 timeslices of 8 sites: one launch of a workgroup per (timeslice, field, spin) would be more
+    threads than a launch may have (2^32)."""
+    dims, nrhs = (2, 2, 2, 258), 65535
+    V = int(np.prod(dims))
+    dl.dl_cache_release()
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 6 * nrhs * V * 192:
+        pytest.skip("needs 156 GB")
+    U = synth.gauge_field(dims, 0.6, seed=981)
+    G = dl.Gauge(dl.Lattice(dims, 1), U)
+    x = torch.zeros((nrhs, V, 4, 3), dtype=torch.complex128, device=dev)
+    at = [0, 1, nrhs // 2, nrhs - 1]
+    psi = synth.random_spinor(dims, len(at), seed=982)
+    for k, r in enumerate(at):
+        x[r] = to_dev(psi[k], dev)
+    out = dl.smear(G, 0.5, 2, x)
+    for k, r in enumerate(at):
+        ref = oracle.smear(U, psi[k], dims, 0.5, 2)
+        assert np.max(np.abs(from_dev(out[r]) - ref)) <= 1e-13 * np.max(np.abs(ref)), r
+    assert not out[2].any()
+    del x, out
+    dl.dl_cache_release()
+    torch.cuda.empty_cache()
