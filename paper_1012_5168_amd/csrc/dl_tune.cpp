@@ -17,10 +17,11 @@
 // lattices) combination is launched, each candidate is timed with HIP events
 // on the real operands (a hopping launch is idempotent when its output
 // aliases no input; the one that updates its y operand in place is timed
-// with its output redirected to a scratch field of the same size); a
-// candidate replaces the default only if it is 3%
-// faster, and the result is kept in memory and in a text cache file
-// (DL_TUNE_CACHE, default ~/.cache/dloops/tune_gfx950_v6.txt).
+// with its output redirected to a scratch field of the same size, so no
+// operand of the solve is written; timed in place, on a field put back
+// afterwards, its candidates take the same times within 1%); a candidate that
+// is faster by a margin (see tune_lookup) replaces the default, and the result
+// is kept in memory and in a text cache file (DL_TUNE_CACHE, default ~/.cache/dloops/tune_gfx950_v6.txt).
 // DL_TUNE=0 disables tuning and uses the default: the LDS-link kernel with 2
 // wavefronts, one wavefront per SIMD and regions of 64 blocks where its links
 // fit in LDS (FP64 with 12-parameter links: 1 wavefront per block, four
@@ -233,31 +234,22 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
     float best_ms = 1e30f;
     std::vector<DslashCall> t = c;
     for (DslashCall &d : t) d.live_count = nullptr;
-    // In-place calls are timed in place on a field that is put back afterwards.
-    std::vector<DevBuf> saved;
-    auto keep = [&](bool back) {
-        for (size_t k = 0; k < saved.size(); ++k) {
-            const DslashCall &d = t[k];
-            const size_t data = (size_t)d.nrhs * rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec));
-            const size_t nrm = d.prec == P16 ? (size_t)d.nrhs * (size_t)d.g.Vh * sizeof(float) : 0;
-            char *sv = saved[k].as<char>();
-            (void)hipMemcpyAsync(back ? d.out.d : sv, back ? sv : d.out.d, data, hipMemcpyDeviceToDevice, s);
-            if (nrm)
-                (void)hipMemcpyAsync(back ? (void *)d.out.nrm : sv + data, back ? sv + data : (char *)d.out.nrm, nrm,
-                                     hipMemcpyDeviceToDevice, s);
-        }
-    };
+    // in-place calls: candidates write a scratch field instead
+    std::vector<DevBuf> scratch;
     if (in_place(c)) {
         try {
-            for (DslashCall &d : t)
-                saved.emplace_back((size_t)d.nrhs * (rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec)) +
-                                                     (d.prec == P16 ? (size_t)d.g.Vh * sizeof(float) : 0)));
+            for (DslashCall &d : t) {
+                const size_t data = (size_t)d.nrhs * rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec));
+                const size_t nrm = d.prec == P16 ? (size_t)d.nrhs * (size_t)d.g.Vh * sizeof(float) : 0;
+                scratch.emplace_back(data + nrm);
+                d.out.d = scratch.back().p;
+                d.out.nrm = nrm ? reinterpret_cast<float *>(static_cast<char *>(scratch.back().p) + data) : nullptr;
+            }
         } catch (...) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return dflt;
         }
-        keep(false);
     }
     std::vector<TuneChoice> cands{dflt};
     for (const TuneChoice &cand : candidates(c[0].prec, c[0].recon))
@@ -287,7 +279,6 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
             best = cand;
         }
     }
-    keep(true);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     g_cache[k] = best;
