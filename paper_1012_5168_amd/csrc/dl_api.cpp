@@ -1011,7 +1011,7 @@ namespace {
 struct SolveWork {
     int n = 0;
     int prec = P64;
-    HalfField be, bo, bhat, x64, xo, r64, tmp64;     // FP64 (BiCGStab)
+    HalfField be, bo, bhat, x64, xo, tmp64;          // FP64 (BiCGStab)
     HalfField r, rh, p, v, t, tmpo, xlo;             // iteration precision
     DevBuf st, flags, parts, parts2;
     // per right-hand side flags, one array after the other: iterating, reliable update due, restart due
@@ -1030,7 +1030,6 @@ struct SolveWork {
         bhat.alloc(P64, n, Vh);
         x64.alloc(P64, n, Vh);
         xo.alloc(P64, n, Vh);
-        r64.alloc(P64, n, Vh);
         tmp64.alloc(P64, n, Vh);
         r.alloc(prec, n, Vh);
         rh.alloc(prec, n, Vh);
@@ -1072,7 +1071,7 @@ struct SolveWork {
     static size_t bytes_bicg(int prec, int64_t Vh)
     {
         size_t f64 = rhs_stride_bytes(Vh, 16), fl = rhs_stride_bytes(Vh, elem_bytes(prec)) + (prec == P16 ? 4 * Vh : 0);
-        return 7 * f64 + (prec == P64 ? 6 : 7) * fl + 8 * 8 * ((Vh + 63) / 64) + 256;
+        return 6 * f64 + (prec == P64 ? 6 : 7) * fl + 8 * 8 * ((Vh + 63) / 64) + 256;
     }
     static size_t bytes_cgnr(int prec, int64_t Vh)
     {
@@ -1477,7 +1476,7 @@ void bicgstab_multi(const std::vector<Prob> &P0, const dl_solve_params &prm, hip
             const std::vector<int> nb64 =
                 launch_dslash_batch(DS(P, [&](const Prob &p) {
                                         DslashCall d = dcall(p.c, P64, 0, false, EPI_REPLACE, p.w->tmp64.view(),
-                                                             p.w->r64.view(), p.w->bhat.view(), p.w->x64.view(),
+                                                             NOF, p.w->bhat.view(), p.w->x64.view(),
                                                              p.kappa * p.kappa, p.w->n, p.w->parts.as<double>(),
                                                              upd(p));
                                         d.lprec = prec;
@@ -1520,13 +1519,14 @@ void bicgstab_batch(const Ctx &c, double kappa, const dl_solve_params &prm, Solv
 }
 
 // Full-lattice FP64 true residual |b - M x|^2 per right-hand side, the even and
-// the odd sites' sums one after the other in `sums` (2 n doubles, device).
+// the odd sites' sums one after the other in `sums` (2 n doubles, device).  The
+// residual itself is not wanted; it goes where the prepared source was.
 void true_residual_full(const Ctx &c, double kappa, SolveWork &w, DevBuf &sums)
 {
     const int n = w.n;
     double *parts = w.parts.as<double>(), *parts2 = w.parts2.as<double>();
     // r_e = b_e - x_e + kappa D_eo x_o ; r_o = b_o - x_o + kappa D_oe x_e
-    int nbd = launch_dslash(dcall(c, P64, 0, false, EPI_XMY_NRM, w.xo.view(), w.r64.view(), w.be.view(), w.x64.view(),
+    int nbd = launch_dslash(dcall(c, P64, 0, false, EPI_XMY_NRM, w.xo.view(), w.bhat.view(), w.be.view(), w.x64.view(),
                                   kappa, n, parts, nullptr),
                             c.s);
     launch_dslash(dcall(c, P64, 1, false, EPI_XMY_NRM, w.x64.view(), w.tmp64.view(), w.bo.view(), w.xo.view(), kappa,

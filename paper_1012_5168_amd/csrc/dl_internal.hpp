@@ -216,8 +216,8 @@ struct DslashCall {
     const int *active;    // per right-hand side flag or null
     unsigned *live_count = nullptr;  // profiling: live right-hand-side blocks
     const struct KState *st = nullptr;  // per right-hand side solver state (EPI_CG_R's alpha)
-    int lprec = 0;               // EPI_REPLACE: the iteration precision and its r, p, rhat (out is then
-    Field lr = {}, lp = {}, lrh = {};  // only what a timing of the launch may write)
+    int lprec = 0;               // EPI_REPLACE: the iteration precision and its r, p, rhat (there is then
+    Field lr = {}, lp = {}, lrh = {};  // no out)
 };
 
 // launch with the tuned (or default) configuration; returns the number of

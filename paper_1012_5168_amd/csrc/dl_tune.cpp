@@ -179,11 +179,11 @@ bool aliases(const std::vector<DslashCall> &cs)
     return false;
 }
 
-// calls that write their y operand in place
-bool in_place(const std::vector<DslashCall> &cs)
+// calls that write their y operand in place, or have no output field (the replacing hop)
+bool needs_scratch(const std::vector<DslashCall> &cs)
 {
     for (const DslashCall &c : cs)
-        if (c.y.d && c.out.d == c.y.d) return true;
+        if (c.out.d == c.y.d || !c.out.d) return true;
     return false;
 }
 
@@ -191,7 +191,7 @@ bool in_place(const std::vector<DslashCall> &cs)
 
 TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
 {
-    // the replacing hop must run once: it is timed as the one that stores its residual
+    // the replacing hop must run once: it is timed as the one that stores its residual (in a scratch field)
     std::vector<DslashCall> c = c0;
     for (DslashCall &d : c)
         if (d.epi == EPI_REPLACE) d.epi = EPI_XMY_NRM;
@@ -237,9 +237,9 @@ TuneChoice tune_lookup(const std::vector<DslashCall> &c0, hipStream_t s)
     float best_ms = 1e30f;
     std::vector<DslashCall> t = c;
     for (DslashCall &d : t) d.live_count = nullptr;
-    // in-place calls: candidates write a scratch field instead
+    // candidates of such calls write a scratch field instead
     std::vector<DevBuf> scratch;
-    if (in_place(c)) {
+    if (needs_scratch(c)) {
         try {
             for (DslashCall &d : t) {
                 const size_t data = (size_t)d.nrhs * rhs_stride_bytes(d.g.Vh, elem_bytes(d.prec));

@@ -136,3 +136,25 @@ def test_freeing_blocks_does_not_hold_up_other_threads(dl, dev):
     releasing.join()
     torch.cuda.synchronize()
     assert took < 0.1 or not waits, took
+
+
+@pytest.mark.parametrize("prec,f64,lower", [(0, 12, 0), (1, 6, 7)])
+def test_workspace_of_a_solve(dl, dev, prec, f64, lower):
+    """Half fields of a BiCGStab workspace: b, prepared b, x and an intermediate in FP64 (two of b and x), r, rhat, p,
+    v, t and an intermediate in the iteration precision, and below FP64 its iterate."""
+    dims, nrhs = (6, 4, 6, 10), 16
+    V = int(np.prod(dims))
+    G = dl.Gauge(dl.Lattice(dims, 1), synth.gauge_field(dims, 0.5, seed=641), precs=(0, prec))
+    b = torch.randn((nrhs, V, 4, 3), dtype=torch.complex128, device=dev)
+    prm = dl.solve_params(prec=prec, tol=1e-10, maxiter=500)
+    dl.solve(G, 0.12, b, prm)  # may time its launches, into a scratch field of its own
+    dl.dl_cache_release()
+    _, st = dl.solve(G, 0.12, b, prm)
+    held = dl.dl_cache_bytes()
+    dl.dl_cache_release()
+    assert all(s[0] == dl.DL_OK and s[3] <= 1e-10 for s in st)
+    # a packed field: 12 planes (6 in FP32) of 16-byte vectors with gaps of 64 between them, and 1 KiB; beside the
+    # fields 64 bytes of sums per right-hand side and block of 64 sites, states, flags and residuals below 512 bytes
+    half = V // 2
+    field = (12 * (half + 64) * 16 + 1024) * f64 + (6 * (half + 64) * 16 + 1024) * lower
+    assert 0 <= held - nrhs * field <= nrhs * (64 * ((half + 63) // 64) + 512), held / nrhs / field
