@@ -227,7 +227,9 @@ typedef struct {
     double bytes;             /* algorithmic bytes of its field operands: every operand of every kernel
                                  its solve ran, moved once (per iteration 23 half fields for BiCGStab,
                                  16 for CGNR, in the iteration precision; per reliable update up to 7
-                                 FP64 and 6 iteration-precision half fields; set-up and reconstruction); the
+                                 FP64 and 6 iteration-precision half fields; set-up and reconstruction; 4
+                                 FP64 half fields, source and solution, where one kernel runs the whole
+                                 solve: BiCGStab in FP64 or FP32 on up to 512 sites per parity); the
                                  links, shared by the batch, are not counted */
 } dl_solve_stats;
 
@@ -465,9 +467,13 @@ uint64_t dl_cache_bytes(void);
  * launches of that kind, their summed event-timed duration and their
  * algorithmic bytes (every operand moved once; for the hopping kernel, the
  * links once per launch plus the in/out/epilogue half spinors of each live
- * right-hand side).  kind: 0 = all hopping kernels, 1 = Krylov vector
+ * right-hand side).  kind: 0 = all hopping kernels, among them the FP64
+ * operators on canonical fields (fields in, fields out, links) and the
+ * one-kernel solves of small lattices, hops and vector updates in one launch
+ * per lattice (sources in, solutions out, links); 1 = Krylov vector
  * kernels, 2 = sources and traces, 3 = the plain (no epilogue, not adjoint)
- * hopping kernel, 4 = smearing.  Returns DL_EINVAL for another kind.
+ * hopping kernel (of dl_apply in FP64: D on canonical fields, both parities in
+ * one launch), 4 = smearing (one launch per step, or one for all of them).  Returns DL_EINVAL for another kind.
  */
 int dl_profile_enable(int32_t on);
 int64_t dl_profile_read(int32_t kind, double *ms, double *bytes);
@@ -482,7 +488,9 @@ int64_t dl_profile_read(int32_t kind, double *ms, double *bytes);
  * allows (0 = as compiled), cfg[3] = persistent grid cap (item kernel, 0 =
  * none) or region size in site blocks (LDS-link kernel); kernel 2 = FP64
  * operators on canonical fields (dl_apply), cfg[1] wavefronts sharing a site
- * block's right-hand sides, cfg[2] = sites per workgroup.  cfg (host, 4 int32) is all -1 when no such launch was profiled since
+ * block's right-hand sides, cfg[2] = sites per workgroup; kernel 3 = one-kernel
+ * solve, cfg[1] right-hand sides per workgroup, cfg[2] = sites per parity.  cfg
+ * (host, 4 int32) is all -1 when no such launch was profiled since
  * dl_profile_enable(1).  Returns DL_EINVAL for another kind or a null cfg.
  */
 int dl_profile_config(int32_t kind, int32_t *cfg);

@@ -1370,7 +1370,14 @@ bool small_solve(const std::vector<Prob> &P, const dl_solve_params &prm, hipStre
         args.push_back(A);
     }
     auto launch = [&](hipStream_t s) {
-        for (size_t k = 0; k < P.size(); ++k) k_small_bicg(prec, P[k].c.G->recon, args[k], P[k].w->n, true, s);
+        for (size_t k = 0; k < P.size(); ++k) {
+            const int recon = P[k].c.G->recon, n = P[k].w->n;
+            // profiled among the hopping kernels: sources in, solutions out, the links of both precisions once
+            const double vh = (double)P[k].Vh(), links = 8.0 * (recon == 12 ? 6 : 9) * vh;
+            ProfScope ps(PROF_DSLASH, 4.0 * 12 * 16 * vh * n + links * (prec == P64 ? 16 : 16 + 8), s);
+            if (prof_on()) prof_config(PROF_DSLASH, -1, TuneChoice{3, 1, (int)P[k].Vh(), 0});
+            k_small_bicg(prec, recon, args[k], n, true, s);
+        }
         DL_HIP(hipGetLastError());
     };
     if (prm.use_graph) {
@@ -1664,10 +1671,12 @@ struct Stopwatch {
 // read, at the start and after a fold.  The set-up and the reconstruction of the odd sites move
 // 10 FP64 half fields (source norms 2, prepared source 3, the start 2: the
 // prepared source read and x cleared, reconstruction 3) and 3 in the iteration
-// precision (r, rhat and p written by the start).
-double solve_bytes(const SolveWork &w, const KState &k, bool cgnr)
+// precision (r, rhat and p written by the start).  A small lattice's one kernel
+// (small_solve) has the sources and the solutions, 4 FP64 half fields.
+double solve_bytes(const SolveWork &w, const KState &k, bool cgnr, bool one_kernel)
 {
     const double vh = (double)w.r.Vh;
+    if (one_kernel) return vh * 4.0 * 12.0 * 16.0;
     const double fb = vh * (12.0 * elem_bytes(w.prec) + (w.prec == P16 ? 4.0 : 0.0));
     if (cgnr) return k.iters * 16.0 * fb + 8.0 * fb;
     const double f8 = vh * 12.0 * 16.0;
@@ -1721,7 +1730,7 @@ struct SolveReport {
             else
                 o.status = DL_ENOCONV;
             o.seconds = secs;
-            o.bytes = solve_bytes(*w, h[i], cgnr);
+            o.bytes = solve_bytes(*w, h[i], cgnr, !split);
         }
     }
 };

@@ -297,3 +297,23 @@ def test_smearing_of_the_most_fields(dl, dev):
     del x, out
     dl.dl_cache_release()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("recon", [12, 18])
+def test_one_kernel_solves_are_profiled(dl, dev, recon, prec):
+    """One launch among the hopping kernels, with the sources, the solutions and the links as its bytes, and the same
+    four half fields in each right-hand side's statistics."""
+    dims, nrhs = (4, 4, 6, 8), 5
+    half = int(np.prod(dims)) // 2
+    G = dl.Gauge(dl.Lattice(dims, 1), synth.gauge_field(dims, 0.5, seed=1001), precs=(0, prec), recon=recon)
+    b = torch.randn((nrhs, 2 * half, 4, 3), dtype=torch.complex128, device=dev)
+    x = torch.empty_like(b)
+    dl.dl_profile_enable(True)
+    _, stats = dl.dl_solve(G.h, 0.12, dl.solve_params(prec=prec, tol=1e-10, maxiter=500), b, x, nrhs)
+    n, ms, by = dl.dl_profile_read(0)
+    cfg = list(dl.dl_profile_config(0))
+    dl.dl_profile_enable(False)
+    assert n == 1 and ms > 0 and cfg == [3, 1, half, 0]
+    assert by == nrhs * 4 * half * 192 + 8 * (6 if recon == 12 else 9) * half * (16 if prec == 0 else 24)
+    assert all(s.status == dl.DL_OK and s.bytes == 4 * half * 192 for s in stats)
