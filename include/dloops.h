@@ -212,7 +212,10 @@ typedef struct {
                             (the first chunk runs eagerly and tunes the launch shapes).  A failure
                             during the capture ends it before the call returns, so the stream is
                             usable again.  For tests of that path, the environment variable
-                            DL_FAULT_INJECT=capture makes every capture fail after it has begun. */
+                            DL_FAULT_INJECT=capture makes every capture fail after it has begun.
+                            Nothing is captured where one kernel runs the whole solve (FP64 or FP32,
+                            every lattice of the call up to 512 sites per parity), but a failure that
+                            is asked for comes all the same. */
 } dl_solve_params;
 
 /* Per right-hand side results of a solve. */

@@ -352,8 +352,7 @@ struct SmallArgs {
     KState *st;
     double *res2;
 };
-// launch = false only raises the kernel's LDS limit (once before the launch, outside a capture)
-void k_small_bicg(int prec, int recon, const SmallArgs &A, int nrhs, bool launch, hipStream_t s);
+void k_small_bicg(int prec, int recon, const SmallArgs &A, int nrhs, hipStream_t s);
 
 // ---------------------------------------------------------------- fields, sources, traces
 

@@ -557,16 +557,14 @@ __global__ __launch_bounds__(NT) void small_bicg_kernel(SmallArgs A)
     }
 }
 
-// the variant for a lattice, to be launched (launch) or only told of its LDS
+// the variant for a lattice
 template <typename S, int NE>
-static void small_go(const SmallArgs &A, int nrhs, bool launch, hipStream_t s)
+static void small_go(const SmallArgs &A, int nrhs, hipStream_t s)
 {
     auto go = [&](auto kernel, int most) {  // most: sites per parity that the variant takes
-        if (launch)
-            hipLaunchKernelGGL(kernel, dim3(nrhs), dim3(NT), (size_t)12 * A.g.Vh * 16, s, A);
-        else
-            DL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 12 * most * 16));
+        DL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   12 * most * 16));
+        hipLaunchKernelGGL(kernel, dim3(nrhs), dim3(NT), (size_t)12 * A.g.Vh * 16, s, A);
     };
     if (A.g.Vh <= NT / 2)
         go(small_bicg_kernel<S, NE, 1, 2>, NT / 2);
@@ -576,18 +574,18 @@ static void small_go(const SmallArgs &A, int nrhs, bool launch, hipStream_t s)
         go(small_bicg_kernel<S, NE, 2, 1>, 2 * NT);
 }
 
-void k_small_bicg(int prec, int recon, const SmallArgs &A, int nrhs, bool launch, hipStream_t s)
+void k_small_bicg(int prec, int recon, const SmallArgs &A, int nrhs, hipStream_t s)
 {
     if (prec == P64) {
         if (recon == 12)
-            small_go<double, 6>(A, nrhs, launch, s);
+            small_go<double, 6>(A, nrhs, s);
         else
-            small_go<double, 9>(A, nrhs, launch, s);
+            small_go<double, 9>(A, nrhs, s);
     } else {
         if (recon == 12)
-            small_go<float, 6>(A, nrhs, launch, s);
+            small_go<float, 6>(A, nrhs, s);
         else
-            small_go<float, 9>(A, nrhs, launch, s);
+            small_go<float, 9>(A, nrhs, s);
     }
 }
 
