@@ -213,18 +213,20 @@ def stream_rates(dl, torch):
     return out
 
 
-def hop_rate(dl, torch, G, nrhs, prec, reps=3):
-    """Plain half-dslash launches of D applied to nrhs right-hand sides at one storage precision:
-    (launches, algorithmic GB/s, mean event-timed launch in us, launch configuration).  The first
-    application tunes; the profiled ones follow."""
+def hop_rate(dl, torch, G, nrhs, prec, reps=6, op=None):
+    """Plain half-dslash launches (the first hop of the Schur operator; with op = D in FP64 the one
+    launch on canonical fields) on nrhs right-hand sides at one storage precision: (launches,
+    algorithmic GB/s, mean event-timed launch in us, launch configuration).  The first application
+    tunes; the profiled ones follow."""
+    op = dl.DL_OP_MHAT if op is None else op
     V = G.lattice.V
     x = torch.zeros((nrhs, V, 4, 3), dtype=torch.complex128, device="cuda")
     x.real.normal_()
-    dl.apply(G, 0.15, dl.DL_OP_DHOP, x, prec=prec)
+    dl.apply(G, 0.15, op, x, prec=prec)
     torch.cuda.synchronize()
     dl.dl_profile_enable(True)
     for _ in range(reps):
-        dl.apply(G, 0.15, dl.DL_OP_DHOP, x, prec=prec)
+        dl.apply(G, 0.15, op, x, prec=prec)
     torch.cuda.synchronize()
     n, ms, by = dl.dl_profile_read(3)
     cfg = dl.dl_profile_config(3)
@@ -235,10 +237,11 @@ def hop_rate(dl, torch, G, nrhs, prec, reps=3):
 
 
 def dslash_sweep(dl, torch, G, copy_gbs):
-    """The plain half dslash D_oe / D_eo at every storage precision on the timed workload's batch
+    """The plain half dslash D_oe at every storage precision on the timed workload's batch
     (16^3 x 32, 288 right-hand sides), the single-right-hand-side FP64 figure on the same lattice
-    (its 75 MB working set sits in the 256 MB Infinity Cache), and the single-right-hand-side FP64
-    figure on 24^3 x 48 (382 MB, larger than that cache)."""
+    (its 75 MB working set sits in the 256 MB Infinity Cache), the single-right-hand-side FP64
+    figure on 24^3 x 48 (382 MB, larger than that cache), and D on canonical FP64 fields
+    (f64_canonical_*, both parities in one launch)."""
     import synth
 
     out = {}
@@ -248,6 +251,10 @@ def dslash_sweep(dl, torch, G, copy_gbs):
         out[nm + "_288rhs"] = {"gbs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4),
                                "frac_copy": round(gbs / copy_gbs, 4), "avg_launch_us": round(us, 1),
                                "launches": n, "config": list(cfg)}
+    for nrhs in (288, 1):
+        n, gbs, us, cfg = hop_rate(dl, torch, G, nrhs, dl.DL_F64, reps=3 if nrhs > 1 else 20, op=dl.DL_OP_DHOP)
+        out["f64_canonical_%drhs" % nrhs] = {"gbs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4),
+                                             "avg_launch_us": round(us, 1), "launches": n, "config": list(cfg)}
     n, gbs, us, cfg = hop_rate(dl, torch, G, 1, dl.DL_F64, reps=20)
     out["f64_1rhs_cache_resident"] = {"gbs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4),
                                       "avg_launch_us": round(us, 1), "launches": n, "config": list(cfg)}
