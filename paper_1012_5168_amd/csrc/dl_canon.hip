@@ -199,9 +199,9 @@ __device__ __forceinline__ void canon_hop(const cx<double> u[9], const cx<double
 // It takes the place of packing, two half hops and unpacking (three times the
 // field traffic).  At 16^3 x 32, M on one field: 102 -> 47 us per call; D on 96
 // fields: 3448 -> 1690 us.  What bounds it there: memory.  The 128 wavefronts
-// of an XCD hold two timeslices at a time and fetch 2.7 times the input (the
+// of an XCD hold two timeslices at a time and fetch 2.4 times the input (the
 // neighbouring timeslices are as many again, and the wavefronts drift apart),
-// 4.8 TB/s with the output.  Tried: one tile in flight instead of two 1.94 ms;
+// 4.9 TB/s with the output.  Tried: one tile in flight instead of two 1.94 ms;
 // projecting before the tile (half the LDS words, but loads of half lines, two
 // fetches of each into L1) 2.5-2.8 ms.
 template <int NE, bool DAG, bool XPAY, bool XIN, bool KEEP>

@@ -309,10 +309,11 @@ __device__ __forceinline__ const char *spinor_base(const Field &f, int64_t Vh, i
 // A scaled format's entry times its site's scale.  As an fma with zero it is one
 // instruction on the 16-bit entry (a mixed-precision fma, 4.5 clocks of a SIMD)
 // instead of a conversion and a product (4.3 and 2.5), with the same rounding.
-// The FP16 hop is bound by the VALU (88% busy): with the temporal links scaled in
-// LDS and no additions to zero, 1064 instead of 1199 instructions a site, 26
-// steps of CGNR on 416 right-hand sides at 16^3 x 32 take 115.6 instead of
-// 116.8 ms of hops.  The products that a projection adds (the upper pair's, UP)
+// With the temporal links scaled in LDS and no additions to zero the plain FP16
+// hop issues 1024 instead of 1156 VALU instructions per right-hand side and 64
+// sites (81 and 93% of the CUs' busy cycles at four cycles each), the residual
+// update 1213 instead of 1369; 416 right-hand sides at 16^3 x 32 take 979
+// instead of 991 us a plain launch and 1320 instead of 1341 us an update.  The products that a projection adds (the upper pair's, UP)
 // stay products: they are contracted into that addition.
 template <typename R, bool UP>
 __device__ __forceinline__ cx<R> scaled_entry(R s, const cx<R> &v)

@@ -135,7 +135,13 @@ struct Own {
 // both sides): 4^4 2.00 -> 0.67 ms (0.45 now), 4^3 x 8 2.11 -> 1.03 (0.81),
 // 4^2 x 6 x 8 2.18 -> 1.45 (1.22); of 288: 2.97 -> 1.15 (0.93), 4.14 -> 2.14
 // (1.92), 4.86 -> 3.30 (3.20).
-// From 648 sites per parity on, the batched kernels' many CUs win.
+// Up to 512 sites it wins at any number of right-hand sides and in both
+// precisions. Loops (kappa 0.145, 1e-10) of 1, 288 and 8192 right-hand sides,
+// this kernel and the batched ones, ms: 128 sites FP64 0.41 / 1.21, 0.88 / 2.05,
+// 13.6 / 23.8, FP32 0.42 / 1.22, 0.90 / 2.02, 14.2 / 16.7; 384 sites FP64 1.12 /
+// 1.50, 2.80 / 3.87, 46.4 / 70.7, FP32 1.03 / 1.46, 2.28 / 3.17, 37.4 / 44.6; 512
+// sites FP64 1.11 / 1.33, 3.18 / 4.50, 56.4 / 78.4, FP32 1.00 / 1.32, 2.44 /
+// 3.55, 40.5 / 51.6.  From 648 on the batched kernels' many CUs win.
 template <typename S, int NE, int K, int WAYS>
 __global__ __launch_bounds__(NT) void small_bicg_kernel(SmallArgs A)
 {
