@@ -158,3 +158,42 @@ def test_workspace_of_a_solve(dl, dev, prec, f64, lower):
     half = V // 2
     field = (12 * (half + 64) * 16 + 1024) * f64 + (6 * (half + 64) * 16 + 1024) * lower
     assert 0 <= held - nrhs * field <= nrhs * (64 * ((half + 63) // 64) + 512), held / nrhs / field
+
+
+def test_threads_share_a_small_cache(dl, dev):
+    """Four threads on streams of their own, each with its lattice and right-hand sides, at a cap that holds about one of
+    their workspaces: blocks are turned away, evicted and freed all the time, and every call gives the bits it gives
+    alone."""
+    work = []
+    for i, (dims, n) in enumerate([((6, 4, 6, 8), 3), ((6, 4, 6, 10), 5), ((8, 4, 6, 8), 2), ((4, 4, 4, 4), 7)]):
+        G = dl.Gauge(dl.Lattice(dims, 1), synth.gauge_field(dims, 0.5, seed=651 + i), precs=(dl.DL_F64, dl.DL_F32))
+        prm = dl.solve_params(prec=i % 2, tol=1e-10, maxiter=500)
+        src = dl.z2_sources(6510 + i, n)
+        dl.loops(G, 0.12, src, [0, 15], prm)  # times its launches
+        work.append((G, prm, src, dl.loops(G, 0.12, src, [0, 15], prm)[0]))
+    wrong, cap = [], 8 << 20
+
+    def run(G, prm, src, ref):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(40):
+                    out, st = dl.loops(G, 0.12, src, [0, 15], prm)
+                    if not np.array_equal(out, ref) or any(s[0] != dl.DL_OK for s in st):
+                        wrong.append(src.seed)
+                    if dl.dl_cache_bytes() > cap:
+                        wrong.append("cap")
+        except Exception as e:
+            wrong.append(repr(e))
+
+    try:
+        dl.dl_cache_release()
+        dl.dl_cache_set_limit(cap)
+        threads = [threading.Thread(target=run, args=w) for w in work]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        dl.dl_cache_set_limit(64 << 30)
+        dl.dl_cache_release()
+    assert not wrong, wrong[:5]
